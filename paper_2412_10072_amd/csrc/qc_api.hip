@@ -351,6 +351,8 @@ qc_status qc_ctx_destroy(qc_ctx* ctx) {
   hipFree(ctx->d_pc_off);
   hipFree(ctx->d_dv);
   hipFree(ctx->d_passes);
+  hipFree(ctx->d_totals);
+  if (ctx->h_done) hipHostFree(ctx->h_done);
   hipFree(ctx->d_done);
   hipFree(ctx->d_active);
   hipFree(ctx->d_pt_int);
@@ -361,6 +363,8 @@ qc_status qc_ctx_destroy(qc_ctx* ctx) {
   hipFree(ctx->d_ddtab);
   hipEventDestroy(ctx->ev0);
   hipEventDestroy(ctx->ev1);
+  for (hipEvent_t ev : ctx->ev_pass)
+    if (ev) hipEventDestroy(ev);
   delete ctx;
   return QC_OK;
 }
@@ -556,6 +560,19 @@ static qc_status solve_interval_impl(qc_ctx* ctx, const qc_vis* vis, qc_term* ch
     P.state.dv = ctx->d_dv;
     P.n_part = parts;
     P.partials = ctx->d_partials;
+    P.totals = nullptr;
+    if (parts > SPLIT_DIRECT_PARTS) {
+      HIP_TRY(ctx, grow(ctx->d_totals, ctx->totals_cap, stride * (size_t)n_int));
+      P.totals = ctx->d_totals;
+    }
+    for (hipEvent_t& ev : ctx->ev_pass)
+      if (!ev) HIP_TRY(ctx, hipEventCreateWithFlags(&ev, hipEventDisableTiming));
+    if (!ctx->h_done) {
+      HIP_TRY(ctx, hipHostMalloc(reinterpret_cast<void**>(&ctx->h_done), sizeof(int), hipHostMallocCoherent));
+      *ctx->h_done = 0;
+    }
+    P.state.all_done = ctx->h_done;
+    P.state.run = ++ctx->split_run;
     P.state.passes = ctx->d_passes;
     P.state.done = ctx->d_done;
     P.state.n_active = ctx->d_active;
@@ -606,10 +623,11 @@ static qc_status solve_interval_impl(qc_ctx* ctx, const qc_vis* vis, qc_term* ch
     for (int k = 0; k < max_rounds && e == hipSuccess; ++k) {
       e = launch_solve(L, &P, s, &lds);
       if (e != hipSuccess) break;
-      int n_active = 0;
-      HIP_TRY(ctx, hipMemcpyAsync(&n_active, ctx->d_active, sizeof(int), hipMemcpyDeviceToHost, s));
-      HIP_TRY(ctx, hipStreamSynchronize(s));
-      if (n_active <= 0) break;
+      // the next pass is launched while this one runs: the host waits for the
+      // pass before it (a pass over intervals that are all done returns at once)
+      HIP_TRY(ctx, hipEventRecord(ctx->ev_pass[k & 1], s));
+      if (k > 0) HIP_TRY(ctx, hipEventSynchronize(ctx->ev_pass[(k - 1) & 1]));
+      if (__atomic_load_n(ctx->h_done, __ATOMIC_ACQUIRE) == P.state.run) break;
     }
   }
   if (e != hipSuccess) {

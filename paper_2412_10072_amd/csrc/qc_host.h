@@ -75,6 +75,11 @@ struct qc_ctx {
   size_t dv_cap = 0;
   int* d_passes = nullptr;
   size_t passes_cap = 0;
+  double* d_totals = nullptr;          // split schedule: the parts of every interval added
+  size_t totals_cap = 0;
+  int* h_done = nullptr;               // pinned: number of the last split solve whose intervals are all done
+  int split_run = 0;                   // split solves started
+  hipEvent_t ev_pass[2] = {nullptr, nullptr};   // the last two passes of a split solve
   uint8_t* d_done = nullptr;
   size_t done_cap = 0;
   int* d_active = nullptr;

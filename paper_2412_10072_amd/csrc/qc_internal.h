@@ -441,6 +441,8 @@ struct SplitState {
   int* passes;                // [n_int] passes accumulated so far
   uint8_t* done;              // [n_int]
   int* n_active;              // intervals not done
+  int* all_done;              // host memory: receives `run` when the last interval is done
+  int run;                    // number of this solve
   double* dv;                 // [n_int][n_ant * NG][2] divergence state per block
   // Levenberg-Marquardt only (else null): per interval the damping, its
   // growth factor, chi^2 at the last accepted gains, the predicted decrease
@@ -469,8 +471,15 @@ struct SplitLaunch {
   int phase;
   int n_part;                 // parts per interval
   double* partials;           // [n_int][n_part][slot values + 1]
+  double* totals;             // [n_int][slot values + 1], n_part > SPLIT_DIRECT_PARTS only
   SplitState state;
 };
+
+// Parts per interval up to which the update's one workgroup adds the parts
+// itself; beyond, k_split_reduce adds them first.
+constexpr int SPLIT_DIRECT_PARTS = 4;
+// Sums every active interval's parts (stride values each) into P.totals.
+hipError_t launch_split_reduce(const SplitLaunch& P, int n_int, size_t stride, hipStream_t stream);
 
 // P == nullptr: the fused schedule (one workgroup runs an interval to the end).
 hipError_t launch_solve(const SolveLaunch& L, const SplitLaunch* P, hipStream_t stream, size_t* lds_bytes_out);

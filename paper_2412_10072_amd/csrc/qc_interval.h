@@ -926,6 +926,23 @@ struct Job {
   const void* dd_tab[BAND_MAX_DD];
 };
 
+// The largest frequency of channels [c_lo, c_hi): band_top_part by every
+// thread, a barrier, then band_top (uses red[0 .. waves)).  The whole workgroup
+// looks: one thread alone took most of an update of 1024-channel intervals.
+__device__ __forceinline__ void band_top_part(const VisArgs& V, int c_lo, int c_hi, double* red) {
+  double m = 0.0;
+  for (int c = c_lo + (int)threadIdx.x; c < c_hi; c += blockDim.x) m = fmax(m, V.freq[c]);
+#pragma unroll
+  for (int o = 32; o >= 1; o >>= 1) m = fmax(m, __shfl_xor(m, o));
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = m;
+}
+__device__ __forceinline__ double band_top(const double* red) {
+  const int nw = blockDim.x >> 6;
+  double m = 0.0;
+  for (int w = 0; w < nw; ++w) m = fmax(m, red[w]);
+  return m;
+}
+
 // LDS bytes the interval solve needs for n_ant antennas and nw waves.
 // lane_rows: steps of one row per lane, which add a claim word per antenna
 // and wave.
@@ -1319,15 +1336,9 @@ __device__ __forceinline__ void solve_interval(const Job& J) {
     gfl[slot] = 0;
   }
   double nu_max = 0.0;
-  if constexpr (is_param(KIND)) {
-    if (threadIdx.x == 0) {
-      double m = 0.0;
-      for (int c = c_lo; c < c_hi; ++c) m = fmax(m, V.freq[c]);
-      red[0] = m;
-    }
-  }
+  if constexpr (is_param(KIND) && !PASS_ONLY) band_top_part(V, c_lo, c_hi, red);   // a lone pass takes no test
   __syncthreads();
-  if constexpr (is_param(KIND)) nu_max = red[0];
+  if constexpr (is_param(KIND) && !PASS_ONLY) nu_max = band_top(red);
 
   // ---- rows of this wave ----
   const long long n_rows = r_hi - r_lo;
@@ -2130,6 +2141,14 @@ __device__ __forceinline__ void solve_interval(const Job& J) {
 // split schedule: the update half of one iteration of one interval
 // ---------------------------------------------------------------------------
 
+// Interval `interval` is done (one thread of its update): the last one of the
+// solve tells the host, which reads the word without waiting for a copy.
+__device__ __forceinline__ void split_finish(const SplitState& St, int interval) {
+  St.done[interval] = 1;
+  if (atomicSub(St.n_active, 1) == 1)
+    __hip_atomic_store(St.all_done, St.run, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 // Levenberg-Marquardt on the split schedule: what the fused loop's LM branch
 // does after a pass, with the interval's state (damping, growth factor, chi^2
 // at the last accepted gains, the pending attempt's predicted decrease, the
@@ -2232,10 +2251,7 @@ __device__ __forceinline__ void split_update_lm(const Job& J, const double* tot,
     if (J.iters) J.iters[interval] = att;
     if (J.converged) J.converged[interval] = conv ? 1 : 0;
     if (J.restarted) J.restarted[interval] = 0;
-    if (finish) {
-      St.done[interval] = 1;
-      atomicSub(St.n_active, 1);
-    }
+    if (finish) split_finish(St, interval);
   }
 }
 
@@ -2288,14 +2304,12 @@ __device__ __forceinline__ void split_update(const Job& J, const double* partial
     double c = 0.0;
     for (int k = 0; k < n_part; ++k) c += partials[k * stride + slot_vals];
     chiw[0] = c;
-    double m = 0.0;
-    if (is_param(KIND))
-      for (int c2 = J.c_lo; c2 < J.c_hi; ++c2) m = fmax(m, V.freq[c2]);
-    red[0] = m;
   }
+  if constexpr (is_param(KIND)) band_top_part(V, J.c_lo, J.c_hi, red);
   __syncthreads();
   const double chi_now = chiw[0];
-  const double nu_max = red[0];
+  double nu_max = 0.0;
+  if constexpr (is_param(KIND)) nu_max = band_top(red);
   const int pass = St.passes[interval];
   if (threadIdx.x == 0) {
     if (pass == 0 && J.chisq_first) J.chisq_first[interval] = chi_now;
@@ -2338,10 +2352,7 @@ __device__ __forceinline__ void split_update(const Job& J, const double* partial
     if (J.iters) J.iters[interval] = iters;
     if (J.converged) J.converged[interval] = conv ? 1 : 0;
     if (J.restarted) J.restarted[interval] = 0;
-    if (finish) {
-      St.done[interval] = 1;
-      atomicSub(St.n_active, 1);
-    }
+    if (finish) split_finish(St, interval);
   }
 }
 

@@ -86,6 +86,38 @@ __global__ void __launch_bounds__(64) k_band_steps(VisArgs V, const long long* r
   steps[r] = s;
 }
 
+// The parts of an interval added per value, the split schedule's step between
+// a pass and the update: one workgroup per (interval, 64 values), its 16
+// wavefronts each adding every 16th part (a 512-byte read per part), then the 16
+// sums in order, so the order of the additions is fixed.  Bound by reading
+// the partials once.  Done by the update's single workgroup per interval before,
+// which read 472 parts of 1537 values (a direction-dependent term, 64 antennas x
+// 4 directions) in 1169 us a pass.
+constexpr int SR_WAVES = 16;
+__global__ void __launch_bounds__(64 * SR_WAVES) k_split_reduce(const double* partials, int n_part, size_t stride,
+                                                                int chunks, const uint8_t* done, double* totals) {
+  __shared__ double part_sum[SR_WAVES][64];
+  const int interval = blockIdx.x / chunks;
+  const int chunk = blockIdx.x - interval * chunks;
+  if (done[interval]) return;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const size_t i = (size_t)chunk * 64 + lane;
+  double sum = 0.0;
+  if (i < stride) {
+    const double* p = partials + (size_t)interval * n_part * stride + i;
+#pragma unroll 4
+    for (int k = wave; k < n_part; k += SR_WAVES) sum += p[(size_t)k * stride];
+  }
+  part_sum[wave][lane] = sum;
+  __syncthreads();
+  if (wave == 0 && i < stride) {
+    double t = 0.0;
+#pragma unroll
+    for (int w = 0; w < SR_WAVES; ++w) t += part_sum[w][lane];
+    totals[(size_t)interval * stride + i] = t;
+  }
+}
+
 // Direction-dependent fixed term j (diagonal gains) by model direction: entry
 // ((g * n_ant + a) * n_dir + d) * 2 + hand, g = gain time * n_gf + gain
 // frequency.  One workgroup per (gain block, antenna), lanes over directions.
@@ -103,6 +135,16 @@ __global__ void __launch_bounds__(64) k_dd_table(TermArgs tm, int n_ant, int n_d
 }
 
 }  // namespace
+
+hipError_t launch_split_reduce(const SplitLaunch& P, int n_int, size_t stride, hipStream_t stream) {
+  const int chunks = (int)((stride + 63) / 64);
+  const long long grid = (long long)n_int * chunks;
+  if (grid == 0) return hipSuccess;
+  if (grid > 0x7fffffffLL) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(k_split_reduce, dim3((unsigned)grid), dim3(64 * SR_WAVES), 0, stream,
+                     (const double*)P.partials, P.n_part, stride, chunks, (const uint8_t*)P.state.done, P.totals);
+  return hipGetLastError();
+}
 
 size_t dd_table_bytes(const SolveLaunch& L, int j) {
   const TermArgs& tm = L.chain.t[j];

@@ -221,6 +221,25 @@ __global__ void k_split_reset(SplitState St, int n_int) {
   if (i == 0) St.n_active[0] = n_int;
 }
 
+// The split update of every active interval after a pass: over the summed
+// partials (P.totals, k_split_reduce) where an interval has more than
+// SPLIT_DIRECT_PARTS parts, else the update adds the parts itself.
+template <typename K>
+hipError_t launch_split_update(K ku, const SolveLaunch& L, const SplitLaunch& P, size_t stride, size_t lds_u,
+                               hipStream_t stream) {
+  const TermArgs& ta = L.chain.t[L.chain.active];
+  const int n_int = ta.n_gt * ta.n_gf;
+  if (P.n_part > SPLIT_DIRECT_PARTS) {
+    hipError_t e = launch_split_reduce(P, n_int, stride, stream);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(ku, dim3((unsigned)n_int), dim3(256), lds_u, stream, L, 1, (const double*)P.totals, P.state);
+  } else {
+    hipLaunchKernelGGL(ku, dim3((unsigned)n_int), dim3(256), lds_u, stream, L, P.n_part,
+                       (const double*)P.partials, P.state);
+  }
+  return hipGetLastError();
+}
+
 // Waves per workgroup: the context's choice; at most 4 for the kernels of
 // wide per-lane state (their launch bound), and for the full-block kernels
 // halved while their per-wave LDS slots (24 values per antenna and gain
@@ -262,8 +281,8 @@ hipError_t launch_split_one(const SolveLaunch& L, const SplitLaunch& P, hipStrea
   } else {
     hipLaunchKernelGGL(kp, dim3((unsigned)(n_int * P.n_part)), dim3(64 * nw), lds, stream, L, P.n_part, P.partials,
                        (const uint8_t*)P.state.done);
-    hipLaunchKernelGGL(ku, dim3((unsigned)n_int), dim3(256), lds_u, stream, L, P.n_part,
-                       (const double*)P.partials, P.state);
+    const size_t stride = (size_t)L.vis.n_ant * NG * nv_of<KIND, FB>() + 1;
+    return launch_split_update(ku, L, P, stride, lds_u, stream);
   }
   return hipGetLastError();
 }
@@ -299,8 +318,7 @@ hipError_t launch_band(const SolveLaunch& L, const SplitLaunch& P, hipStream_t s
       kern = L.n_dd == 0 ? k_band_pass<S, T, 0, 16> : L.n_dd == 1 ? k_band_pass<S, T, 1, 16> : k_band_pass<S, T, 2, 16>;
     }
     hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(64), lds, stream, L, P.n_part, P.partials, done);
-    hipLaunchKernelGGL(ku, dim3((unsigned)n_int), dim3(256), lds_u, stream, L, P.n_part,
-                       (const double*)P.partials, P.state);
+    return launch_split_update(ku, L, P, (size_t)L.vis.n_ant * BAND_NV + 1, lds_u, stream);
   }
   return hipGetLastError();
 }
