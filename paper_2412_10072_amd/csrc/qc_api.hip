@@ -391,6 +391,59 @@ double qc_last_kernel_ms(qc_ctx* ctx) {
 
 }  // extern "C"
 
+// Parts per interval of a solve (1: the fused schedule), by an estimate of
+// one pass of each schedule in microseconds.
+//
+// Fused: a workgroup of four wavefronts takes an interval of its own, so a pass
+// takes at least its steps one after the other; where n_int is no multiple of
+// the workgroups the chip holds, the last ones run with the chip half empty.
+// Split: the same work spread over the chip, plus the launches, the sums of the
+// parts and an update kernel.  Measured (MI355X, whole solves, fused against
+// split): 35 diagonal intervals of 1.6e5 samples 9.1 / 1.1 ms; 80 full-Jones
+// ones of 1.3e5 5.5 / 1.5 ms; 1100 of them 19.2 / 16.2 ms, 1600 22.0 / 22.0; 640
+// diagonal ones 8.6 / 8.9 ms; 400 of 3040 samples 0.37 / 0.49 ms; 4 of 19200
+// samples 1.13 / 0.35 ms; one delay interval of 5.7e5 samples x 3 directions
+// 201 / 1.1 ms.  Constants: a step of a lone workgroup takes 1.2-1.4 us in
+// the single-term kernels, 3.6-5.1 us in the chain kernels over 3-4
+// directions and 9-11 us with one row per lane; a pass with its update costs about
+// 12 us beyond its steps fused and 25 us split.  Levenberg-Marquardt keeps to large
+// intervals (2^18 samples on average): its accepted steps hang on the last bits
+// of chi^2, which differ between the schedules.
+static int split_parts(const qc_ctx* ctx, const qc_vis* vis, const qc_term& ta, int n_term, const SolveLaunch& L,
+                       bool lm) {
+  const int n_int = ta.n_gt * ta.n_gf;
+  const double n_samples = (double)vis->n_row * vis->n_chan;
+  const double rows = (double)vis->n_row / std::max(ta.n_gt, 1);
+  const double avg = n_samples / n_int;
+  const bool single = n_term == 1 && vis->n_dir == 1 && ta.n_gdir == 1;
+  const bool fp64 = !L.prec_mixed;
+  const bool lane_rows = !single && L.max_int_chan <= 4 && ta.n_gdir == 1 && !L.left_general;
+  const int rps = single ? 4 : lane_rows ? 64 : 1;
+  const double chunks = lane_rows ? L.max_int_chan : std::ceil(L.max_int_chan / (64.0 / rps));
+  const double steps = std::ceil(rows / (4.0 * rps)) * chunks;
+  const double step_us = single ? 1.25 : lane_rows ? 10.0 : 1.25 * (1.0 + 0.75 * vis->n_dir);
+  const int fit = ctx->n_cu * (fp64 ? 2 : single ? 4 : 3);
+  const double real = L.vis_is_c128 ? 8.0 : 4.0;
+  const double pass_bytes = n_samples * (real * (8.0 + 8.0 * vis->n_dir + vis->n_wcorr) + 1.0);
+  const double stream_us = pass_bytes / 6e6;                     // 6 TB/s
+  const bool large = n_int < 4 * ctx->n_cu && avg >= (double)(1 << 18);   // split whatever the estimate
+  if (lm && !large) return 1;
+  if (!large) {
+    const int full = n_int / fit, rest = n_int - full * fit;
+    const double fused_us = 12.0 + full * std::max(stream_us * fit / n_int, steps * step_us) +
+                            (rest ? std::max(stream_us * rest / n_int, steps * step_us) : 0.0);
+    const double split_us = 25.0 + std::max(stream_us, n_int * steps * step_us / fit);
+    if (fused_us <= 1.1 * split_us + 10.0) return 1;
+  }
+  double wg = std::min((double)SPLIT_WG_PER_CU, std::max((double)SPLIT_WG_PER_CU_MIN,
+                                                         n_samples / SPLIT_PART_SAMPLES / ctx->n_cu));
+  const double most = std::max(2.0, std::min(rows / SPLIT_MIN_ROWS, avg / SPLIT_MIN_SAMPLES));
+  const int parts = (int)std::max(2.0, std::min(std::ceil(wg * ctx->n_cu / n_int), std::floor(most)));
+  // the partial sums (24 values per block at most) stay below 2 GiB
+  const double blocks = (double)n_int * parts * vis->n_ant * (ta.n_gdir == 1 ? 1 : 4);
+  return blocks * 24.0 * sizeof(double) > 2147483648.0 ? 1 : parts;
+}
+
 // qc_solve_interval; fixed != NULL: the allocation-free form (prepare scratch
 // in `fixed`, always the fused schedule, no fixed-factor table, no pointing);
 // sky != NULL: the model predicted from point components in the passes
@@ -480,12 +533,9 @@ static qc_status solve_interval_impl(qc_ctx* ctx, const qc_vis* vis, qc_term* ch
   for (int d = 0; L.dir_ident && d < vis->n_dir; ++d)
     if (maps[active].d_map[d] != d) L.dir_ident = 0;
   L.rows_per_step = ctx->rows_per_step == 8 ? 0 : ctx->rows_per_step;   // 8: the one-channel split only
-  // schedule: fused (one workgroup per interval) unless the term has too few
-  // intervals to give every CU several workgroups and they are large enough
-  // (>= 2^18 samples on average) to amortise a host wait per iteration; those
-  // are cut into parts streamed by separate workgroups (about SPLIT_WG_PER_CU per CU)
+  // schedule: fused (one workgroup per interval) or split (each interval's rows
+  // streamed by several workgroups), by split_parts
   const int n_int = ta.n_gt * ta.n_gf;
-  const double avg_samples = n_int > 0 ? (double)vis->n_row * vis->n_chan / n_int : 0.0;
   int parts = 1;
   const bool lm = opts->damping == QC_DAMP_LM;
   if (lm && ta.type == QC_TERM_DELAY_OFFSET)
@@ -494,11 +544,8 @@ static qc_status solve_interval_impl(qc_ctx* ctx, const qc_vis* vis, qc_term* ch
     parts = 1;                                 // the split schedule's state is context memory
   } else if (ctx->split_parts > 1) {
     parts = ctx->split_parts;
-  } else if (ctx->split_parts == 0 && !opts->chisq_ref && n_int > 0 && n_int < 4 * ctx->n_cu &&
-             avg_samples >= (double)(1 << 18)) {
-    const double rows_per_int = (double)vis->n_row / std::max(ta.n_gt, 1);
-    parts = (int)std::ceil((double)SPLIT_WG_PER_CU * ctx->n_cu / n_int);
-    parts = std::max(2, std::min(parts, (int)std::max(1.0, rows_per_int / 64.0)));
+  } else if (ctx->split_parts == 0 && !opts->chisq_ref && n_int > 0) {
+    parts = split_parts(ctx, vis, ta, n_term, L, lm);
   }
   if (parts > 1 && opts->chisq_ref)
     return fail(ctx, QC_E_UNSUPPORTED, "the split schedule does not take chisq_ref");
@@ -531,7 +578,7 @@ static qc_status solve_interval_impl(qc_ctx* ctx, const qc_vis* vis, qc_term* ch
     const long long units = (long long)((vis->n_chan + 64 / L.band_rows - 1) / (64 / L.band_rows)) * ta.n_gt;
     const double rows_per_int = (double)vis->n_row / std::max(ta.n_gt, 1);
     parts = (int)std::ceil((double)BAND_WAVES_PER_CU * ctx->n_cu / (double)units);
-    parts = std::max(2, std::min(parts, (int)std::max(1.0, rows_per_int / 64.0)));
+    parts = std::max(2, std::min(parts, (int)std::max(1.0, rows_per_int / 32.0)));
   }
   ctx->last_split_parts = parts;
   // diagonal chains: the direction-independent terms other than the active

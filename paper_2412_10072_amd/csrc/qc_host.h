@@ -11,11 +11,22 @@
 
 #include "qc_internal.h"
 
-// Workgroups per compute unit that the automatic split aims at: the split
-// passes are latency-bound, and the chain workload's terms (delay,
-// bandpass, gain, direction-dependent) and the pointing and delay-offset
-// solves ran 10-30% faster at about 32 than at 4 (measured; flat beyond).
+// The automatic split aims at SPLIT_WG_PER_CU_MIN workgroups per compute unit,
+// and at up to SPLIT_WG_PER_CU where parts of SPLIT_PART_SAMPLES samples give so
+// many: 1.2e8 samples and more are streamed 10-30% faster in about 32 small
+// parts per CU than in 4 (flat beyond), while at 3e7 samples and below 4 to 8
+// per CU are as fast and leave fewer partial sums (chain workload, 64
+// antennas: the direction-dependent term's solve 26.6 ms in 1024 parts, 28.3 in
+// 8192).  A part has at least SPLIT_MIN_SAMPLES samples and SPLIT_MIN_ROWS rows
+// (one step of every wavefront): a delay solve over 5.7e5 samples in one interval
+// takes 1.1 ms in 512 parts of 1100 samples, 2.2 ms in 128.
+// The pointing solve, whose passes have a schedule of their own, always takes
+// SPLIT_WG_PER_CU.
 constexpr int SPLIT_WG_PER_CU = 32;
+constexpr int SPLIT_WG_PER_CU_MIN = 4;
+constexpr double SPLIT_PART_SAMPLES = 32768.0;
+constexpr double SPLIT_MIN_SAMPLES = 512.0;
+constexpr double SPLIT_MIN_ROWS = 16.0;
 // Wavefronts per compute unit that the split over one-channel intervals aims
 // at (each holds 16 intervals and 24 KiB of LDS at 64 antennas, so about six
 // are resident per CU: two rounds of them; 6 to 48 measured within 6%)
