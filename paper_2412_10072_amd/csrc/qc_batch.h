@@ -38,6 +38,40 @@ struct BatchArgs {
   int* err;
 };
 
+// A team item: an interval whose rows are streamed in parts by any number of
+// workgroups (k_batch_team).
+struct TeamItem {
+  BatchItem it;
+  long long part_off;          // doubles before the item's parts in TeamArgs::parts
+  long long dv_off;            // doubles before its divergence state
+  int n_part, n_group;         // parts, and groups of TEAM_GROUP parts added together
+};
+
+constexpr int TEAM_GROUP = 8;
+constexpr int TEAM_MAX_PARTS = 64;                                // TEAM_MAX_PARTS / TEAM_GROUP group counters
+// Words of an item, a 64-byte line: the next part to be claimed (low half) of
+// the pass under way (high half; open while the low half is below n_part), the
+// groups arrived, then the parts arrived per group.
+struct TeamWords {
+  unsigned long long next;
+  int groups;
+  int parts[TEAM_MAX_PARTS / TEAM_GROUP];
+  int pad[16 - 3 - TEAM_MAX_PARTS / TEAM_GROUP];
+};
+static_assert(sizeof(TeamWords) == 64, "one line per item");
+
+struct TeamArgs {
+  const BatchProb* probs;
+  const TeamItem* items;
+  int n_items;
+  TeamWords* words;            // [n_items + 1]; the last one's `groups`: items done
+  double* parts;               // per item [n_part + n_group][slot values + 1]
+  double* dv;
+  double tol;
+  int max_iter;
+  int* err;
+};
+
 // A wave-uniform copy of *src (the same in every lane): every 32-bit word
 // read and broadcast from the first lane, so that a problem's pointers and
 // sizes can live in scalar registers (a struct read from device memory at an
@@ -64,5 +98,9 @@ size_t ws_features_lds(int n_ant, int waves);
 size_t batch_lds_bytes(int prec_mixed, int max_ant, int waves);
 hipError_t launch_batch_bucket(const BatchArgs& B, void* kern, int waves, size_t lds, int grid, hipStream_t s);
 hipError_t launch_zero_ints(int* p, int n, hipStream_t s);
+// the team kernel over `grid` workgroups of 4 wavefronts, after its reset
+void* team_kernel_ptr(int prec_mixed, int vis_c128);
+size_t team_lds_bytes(int prec_mixed, int max_ant);
+hipError_t launch_batch_team(const TeamArgs& A, void* kern, size_t lds, int grid, hipStream_t s);
 
 }  // namespace qc

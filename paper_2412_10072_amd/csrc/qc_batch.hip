@@ -108,6 +108,164 @@ k_solve_batch(BatchArgs B) {
   }
 }
 
+// Intervals too large for one workgroup: teams.
+//
+// A lone workgroup streams an interval at about 10 GB/s, so in a batch of
+// uneven problems the largest intervals run long after the rest is done (24
+// problems of 5 GB in all: one of 12 wide intervals took 38 of the 50 ms).
+// Here an interval's rows are cut into parts that any workgroup may take.  A
+// workgroup claims an open part (of the item it worked on last, else of the
+// next one that has any), streams it at the current gains and writes its FP64
+// block.  The workgroup that completes a group of TEAM_GROUP parts adds the
+// group, and the one that completes the item's groups adds those, in index
+// order, updates the gains and opens the next pass, so sums do not depend on
+// timing, and no pass needs the host or a launch.  A workgroup without a part
+// waits only while some item is neither done nor fully claimed by running
+// workgroups: every claimed part is being streamed, and an item ends after at
+// most max_iter + 1 passes, so every wait ends however many workgroups are
+// resident.
+template <int KIND, typename S, typename T>
+__device__ __forceinline__ bool team_part(const Job& J, const TeamArgs& A, const TeamItem& I, TeamWords* words, int part,
+                                          int pass, int* s_last) {
+  constexpr int NV = nv_of<KIND, false>();
+  const int tid = threadIdx.x;
+  const size_t stride = (size_t)J.V->n_ant * NV + 1;
+  double* parts = A.parts + I.part_off;
+  Job P = J;
+  const long long n = I.it.r_hi - I.it.r_lo;
+  P.r_lo = I.it.r_lo + (n * part) / I.n_part;
+  P.r_hi = I.it.r_lo + (n * (part + 1)) / I.n_part;
+  P.partial = parts + (size_t)part * stride;
+  solve_interval<KIND, S, T, CHAIN_SINGLE, 1, 4, true, false, false, 2, true>(P);
+  team_release();                              // the part, before it is counted
+  const int g = part / TEAM_GROUP, g0 = g * TEAM_GROUP;
+  const int g_parts = min(TEAM_GROUP, I.n_part - g0);
+  if (tid == 0) *s_last = (atomicAdd(&words->parts[g], 1) + 1) % g_parts == 0;
+  __syncthreads();
+  if (!*s_last) return false;
+  const double* src = parts;
+  int n_src = I.n_part;
+  if (I.n_group > 1) {
+    double* sums = parts + (size_t)I.n_part * stride;
+    for (size_t i = tid; i < stride; i += blockDim.x) {
+      double x = 0.0;
+      for (int k = g0; k < g0 + g_parts; ++k) x += ld_shared<true>(parts + (size_t)k * stride + i);
+      st_shared<true>(sums + (size_t)g * stride + i, x);
+    }
+    team_release();
+    if (tid == 0) *s_last = (atomicAdd(&words->groups, 1) + 1) % I.n_group == 0;
+    __syncthreads();
+    if (!*s_last) return false;
+    src = sums;
+    n_src = I.n_group;
+  }
+  const bool done = split_update_at<KIND, T, 1, false, true>(J, src, n_src, A.dv + I.dv_off, pass, nullptr);
+  team_release();                              // the gains, before the next pass opens
+  if (tid == 0 && !done) st_shared<true>(&words->next, (unsigned long long)(pass + 1) << 32);
+  return done;
+}
+
+// An open part of some item, by one wavefront: 64 items are looked at together,
+// from `from` on, and an open one's part is taken by one addition (a
+// compare-and-swap had hundreds of waiting workgroups repeat it for each part
+// of a pass that opened: 480 us a pass for 6 items of a few parts).  Returns the
+// item, pass and part; -1 when every item is done.
+__device__ __forceinline__ int team_claim(const TeamArgs& A, int from, int lane, int& pass, int& part) {
+  for (;;) {
+    for (int base = 0; base < A.n_items; base += 64) {
+      const bool in = base + lane < A.n_items;
+      int idx = from + base + lane;
+      if (idx >= A.n_items) idx -= A.n_items;
+      if (!in) idx = 0;
+      TeamWords* w = A.words + idx;
+      const unsigned n_part = (unsigned)A.items[idx].n_part;
+      const unsigned next = (unsigned)ld_shared<true>(&w->next);
+      unsigned long long mask = __ballot(in && next < n_part);
+      while (mask) {
+        const int l = __ffsll(mask) - 1;
+        unsigned long long got = 0;
+        if (lane == l) got = atomicAdd(&w->next, 1ull);
+        const unsigned mine = (unsigned)__shfl((int)(unsigned)got, l);
+        if (mine < (unsigned)__shfl((int)n_part, l)) {
+          part = (int)mine;
+          pass = __shfl((int)(unsigned)(got >> 32), l);
+          return __shfl(idx, l);
+        }
+        mask &= mask - 1;
+      }
+    }
+    if (ld_shared<true>(&A.words[A.n_items].groups) >= A.n_items) return -1;
+    __builtin_amdgcn_s_sleep(64);
+  }
+}
+
+template <typename S, typename T>
+__global__ void __launch_bounds__(256) k_batch_team(TeamArgs A) {
+  __shared__ int s_item, s_pass, s_part, s_last;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int lane = threadIdx.x & 63;
+  int from = (int)((long long)blockIdx.x * A.n_items / gridDim.x);
+  for (;;) {
+    if (wave == 0) {
+      int pass = 0, part = 0;
+      const int k = team_claim(A, from, lane, pass, part);
+      if (lane == 0) {
+        s_item = k;
+        s_pass = pass;
+        s_part = part;
+      }
+    }
+    __syncthreads();
+    const int item = __builtin_amdgcn_readfirstlane(s_item);
+    const int pass = __builtin_amdgcn_readfirstlane(s_pass), part = __builtin_amdgcn_readfirstlane(s_part);
+    __syncthreads();
+    if (item < 0) break;
+    from = item;
+    const TeamItem I = uniform_copy(A.items + item);
+    const BatchProb P = uniform_copy(A.probs + I.it.prob);
+    Job J;
+    J.V = &P.vis;
+    J.CH = nullptr;
+    J.TA = &P.term;
+    J.gains = P.gains;
+    J.params = nullptr;
+    J.gflags = P.gflags;
+    J.iters = P.iters;
+    J.converged = P.converged;
+    J.chisq_first = P.chisq_first;
+    J.chisq_last = P.chisq_last;
+    J.gt = I.it.gt;
+    J.gf = I.it.gf;
+    J.n_gf = P.term.n_gf;
+    J.c_lo = I.it.c_lo;
+    J.c_hi = I.it.c_hi;
+    J.r_lo = I.it.r_lo;
+    J.r_hi = I.it.r_hi;
+    J.tol = A.tol;
+    J.max_iter = A.max_iter;
+    J.damping = P.damping;
+    J.err = A.err;
+    J.chisq_ref = nullptr;
+    J.restarted = P.restarted;
+    J.partial = nullptr;
+    J.otab = nullptr;
+    J.sky = nullptr;
+    J.restart_flag = nullptr;
+    J.n_dd = -1;
+    TeamWords* words = A.words + item;
+    bool done;
+    if (P.term.kind == KIND_DIAG) done = team_part<KIND_DIAG, S, T>(J, A, I, words, part, pass, &s_last);
+    else done = team_part<KIND_C2X2, S, T>(J, A, I, words, part, pass, &s_last);
+    if (done && threadIdx.x == 0) atomicAdd(&A.words[A.n_items].groups, 1);
+    __syncthreads();                           // s_last is read by every thread before it is set again
+  }
+}
+
+__global__ void k_team_reset(int n_items, TeamWords* words) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i <= n_items) words[i] = TeamWords{};
+}
+
 __global__ void k_zero_ints(int* p, int n) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n) p[i] = 0;
@@ -146,6 +304,29 @@ hipError_t launch_batch_bucket(const BatchArgs& B, void* kern, int waves, size_t
   if (B.n_items <= 0) return hipSuccess;
   void* args[] = {const_cast<BatchArgs*>(&B)};
   return hipLaunchKernel(kern, dim3(grid), dim3(64 * waves), args, lds, s);
+}
+
+void* team_kernel_ptr(int prec_mixed, int vis_c128) {
+  if (prec_mixed) return reinterpret_cast<void*>(k_batch_team<float, float>);
+  if (vis_c128) return reinterpret_cast<void*>(k_batch_team<double, double>);
+  return reinterpret_cast<void*>(k_batch_team<float, double>);
+}
+
+// the larger of a pass of 4 wavefronts and an update with its divergence state
+size_t team_lds_bytes(int prec_mixed, int max_ant) {
+  const size_t dv = sizeof(double) * 2 * (size_t)max_ant;
+  if (prec_mixed)
+    return std::max(interval_lds_bytes<KIND_C2X2, float, 1>(max_ant, 4), team_dv_off<KIND_C2X2, float>(max_ant) + dv);
+  return std::max(interval_lds_bytes<KIND_C2X2, double, 1>(max_ant, 4), team_dv_off<KIND_C2X2, double>(max_ant) + dv);
+}
+
+hipError_t launch_batch_team(const TeamArgs& A, void* kern, size_t lds, int grid, hipStream_t s) {
+  if (A.n_items <= 0) return hipSuccess;
+  hipLaunchKernelGGL(k_team_reset, dim3(A.n_items / 256 + 1), dim3(256), 0, s, A.n_items, A.words);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  void* args[] = {const_cast<TeamArgs*>(&A)};
+  return hipLaunchKernel(kern, dim3(grid), dim3(256), args, lds, s);
 }
 
 hipError_t launch_zero_ints(int* p, int n, hipStream_t s) {

@@ -3,6 +3,7 @@
 // autotuner that picks (waves per workgroup, rows per step) per bucket by
 // timing the candidates on the batch itself.
 
+#include <cmath>
 #include <numeric>
 
 #include "qc_batch.h"
@@ -27,7 +28,20 @@ struct Bucket {
   int grid = 0;
   size_t lds = 0;
   float ms = -1.f;     // tuned time (ms), negative if untuned
+  int team = 0;        // intervals of this width and size class that the team kernel solves
 };
+
+// Passes that the estimates below reckon with (MeerKAT-like solves to 1e-6
+// take 8 to 15), the streaming rate, and the steps of 4 wavefronts from which
+// an interval may be a team's: a lone workgroup of 8 wavefronts takes about
+// 12 us a pass beyond half a step_us per step, a team 25 us.
+constexpr double EST_PASSES = 10.0;
+constexpr double EST_BYTES_PER_US = 6e6;
+constexpr double EST_STEP_US = 1.3;
+constexpr double TEAM_MIN_STEPS = 48.0;
+// An interval is a team's where one workgroup would take longer for it than
+// this share of the whole batch streamed at full rate.
+constexpr double TEAM_SHARE = 0.25;
 
 }  // namespace
 
@@ -48,12 +62,19 @@ struct qc_batch {
   int* d_queue = nullptr;                 // [N_BUCKET]
   Bucket bucket[N_BUCKET];
   hipStream_t cs = nullptr;               // capture stream
-  hipStream_t bs[N_BUCKET] = {};
-  hipEvent_t fork = nullptr, join[N_BUCKET] = {};
+  hipStream_t bs[N_BUCKET + 1] = {};      // the buckets, the teams
+  hipEvent_t fork = nullptr, join[N_BUCKET + 1] = {};
   hipEvent_t t0 = nullptr, t1 = nullptr;
   hipGraph_t graph = nullptr;
   hipGraphExec_t exec = nullptr;
   int n_cu = 256;
+  // intervals solved by teams of workgroups (the first n_team of d_items)
+  int n_team = 0, team_grid = 0;
+  size_t team_lds = 0;
+  TeamItem* d_team = nullptr;
+  TeamWords* d_team_words = nullptr;
+  double* d_team_parts = nullptr;
+  double* d_team_dv = nullptr;
 };
 
 namespace {
@@ -96,6 +117,85 @@ qc_status launch_bucket(qc_batch* b, int i, hipStream_t s) {
   return QC_OK;
 }
 
+qc_status launch_team(qc_batch* b, hipStream_t s) {
+  if (b->n_team == 0) return QC_OK;
+  TeamArgs a;
+  a.probs = b->d_probs;
+  a.items = b->d_team;
+  a.n_items = b->n_team;
+  a.words = b->d_team_words;
+  a.parts = b->d_team_parts;
+  a.dv = b->d_team_dv;
+  a.tol = b->tol;
+  a.max_iter = b->max_iter;
+  a.err = b->ctx->d_err;
+  HIP_TRY(b->ctx, launch_batch_team(a, team_kernel_ptr(b->prec_mixed, b->vis_c128), b->team_lds, b->team_grid, s));
+  return QC_OK;
+}
+
+// Which intervals are a team's (true in `team`): those that one workgroup would
+// still be at long after the rest of the batch is done.  A problem with a
+// warm-start reference keeps its intervals whole (its restart is the bucket
+// kernels'), and Levenberg-Marquardt batches do.
+void choose_team(const qc_batch* b, const std::vector<BatchItem>& items, std::vector<char>& team) {
+  team.assign(items.size(), 0);
+  if (b->lm) return;
+  double total_us = 0.0;
+  const double real = b->vis_c128 ? 8.0 : 4.0;
+  for (const BatchItem& it : items)
+    total_us += EST_PASSES * (double)(it.r_hi - it.r_lo) * (it.c_hi - it.c_lo) *
+                (real * (16.0 + b->probs[it.prob].vis.n_wcorr) + 1.0) / EST_BYTES_PER_US;
+  for (size_t k = 0; k < items.size(); ++k) {
+    const BatchItem& it = items[k];
+    if (b->probs[it.prob].chisq_ref) continue;
+    const double steps = std::ceil((it.r_hi - it.r_lo) / 16.0) * std::ceil((it.c_hi - it.c_lo) / 16.0);
+    const double alone_us = EST_PASSES * (12.0 + 0.5 * EST_STEP_US * steps);
+    team[k] = steps >= TEAM_MIN_STEPS && alone_us > TEAM_SHARE * total_us;
+  }
+}
+
+// The team items (the first n_team of `items`), their parts and device memory.
+qc_status make_team(qc_batch* b, const std::vector<BatchItem>& items) {
+  qc_ctx* ctx = b->ctx;
+  if (b->n_team == 0) return QC_OK;
+  double samples = 0.0;
+  for (int k = 0; k < b->n_team; ++k) samples += (double)(items[k].r_hi - items[k].r_lo) * (items[k].c_hi - items[k].c_lo);
+  // parts of 2048 to 32768 samples, about 8 per compute unit
+  const double per_part = std::min(32768.0, std::max(2048.0, samples / (8.0 * b->n_cu)));
+  std::vector<TeamItem> team(b->n_team);
+  long long parts = 0, dv = 0, n_parts = 0;
+  for (int k = 0; k < b->n_team; ++k) {
+    TeamItem& t = team[k];
+    t.it = items[k];
+    const double rows = (double)(t.it.r_hi - t.it.r_lo);
+    const double want = std::min(rows * (t.it.c_hi - t.it.c_lo) / per_part, rows / 16.0);
+    t.n_part = (int)std::max(2.0, std::min((double)TEAM_MAX_PARTS, std::ceil(want)));
+    t.n_group = (t.n_part + TEAM_GROUP - 1) / TEAM_GROUP;
+    const BatchProb& P = b->probs[t.it.prob];
+    const long long stride = (long long)P.vis.n_ant * (P.term.kind == KIND_C2X2 ? 16 : 6) + 1;   // KindInfo NV
+    t.part_off = parts;
+    parts += stride * (t.n_part + t.n_group);
+    t.dv_off = dv;
+    dv += 2LL * P.vis.n_ant;
+    n_parts += t.n_part;
+  }
+  if (hipMalloc(reinterpret_cast<void**>(&b->d_team), sizeof(TeamItem) * team.size()) != hipSuccess ||
+      hipMalloc(reinterpret_cast<void**>(&b->d_team_words), sizeof(TeamWords) * (team.size() + 1)) != hipSuccess ||
+      hipMalloc(reinterpret_cast<void**>(&b->d_team_parts), sizeof(double) * parts) != hipSuccess ||
+      hipMalloc(reinterpret_cast<void**>(&b->d_team_dv), sizeof(double) * dv) != hipSuccess)
+    return fail(ctx, QC_E_NOMEM, "batch team memory");
+  HIP_TRY(ctx, hipMemcpy(b->d_team, team.data(), sizeof(TeamItem) * team.size(), hipMemcpyHostToDevice));
+  void* kern = team_kernel_ptr(b->prec_mixed, b->vis_c128);
+  b->team_lds = team_lds_bytes(b->prec_mixed, b->max_ant);
+  if (b->team_lds > 160 * 1024) return fail(ctx, QC_E_UNSUPPORTED, "batch needs %zu B of LDS", b->team_lds);
+  if (b->team_lds > 64 * 1024)
+    HIP_TRY(ctx, hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)b->team_lds));
+  int per_cu = 0;
+  HIP_TRY(ctx, hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, 256, b->team_lds));
+  b->team_grid = (int)std::min<long long>(n_parts, (long long)b->n_cu * std::max(per_cu, 1));
+  return QC_OK;
+}
+
 void drop_graph(qc_batch* b) {
   if (b->exec) hipGraphExecDestroy(b->exec);
   if (b->graph) hipGraphDestroy(b->graph);
@@ -103,8 +203,8 @@ void drop_graph(qc_batch* b) {
   b->graph = nullptr;
 }
 
-// One graph: zero the queue counters, then every non-empty bucket on its own
-// branch, joined back into the capture stream.
+// One graph: zero the queue counters, then the teams and every non-empty bucket
+// on branches of their own, joined back into the capture stream.
 qc_status build_graph(qc_batch* b) {
   qc_ctx* ctx = b->ctx;
   drop_graph(b);
@@ -112,11 +212,12 @@ qc_status build_graph(qc_batch* b) {
   qc_status st = QC_OK;
   hipError_t e = launch_zero_ints(b->d_queue, N_BUCKET, b->cs);
   if (e == hipSuccess) e = hipEventRecord(b->fork, b->cs);
-  for (int i = 0; i < N_BUCKET && e == hipSuccess; ++i) {
-    if (b->bucket[i].count == 0) continue;
+  for (int j = 0; j <= N_BUCKET && e == hipSuccess; ++j) {
+    const int i = j == 0 ? N_BUCKET : j - 1;        // the teams' branch first
+    if (i == N_BUCKET ? b->n_team == 0 : b->bucket[i].count == 0) continue;
     e = hipStreamWaitEvent(b->bs[i], b->fork, 0);
     if (e == hipSuccess) {
-      st = launch_bucket(b, i, b->bs[i]);
+      st = i == N_BUCKET ? launch_team(b, b->bs[i]) : launch_bucket(b, i, b->bs[i]);
       if (st != QC_OK) break;
     }
     if (e == hipSuccess) e = hipEventRecord(b->join[i], b->bs[i]);
@@ -223,7 +324,9 @@ qc_status qc_batch_create(qc_ctx* ctx, const qc_problem* problems, int32_t n_pro
         items.push_back(it);
       }
   }
-  // bucket, then largest first inside a bucket
+  // the teams' items, then the buckets', largest first in each
+  std::vector<char> team;
+  choose_team(b, items, team);
   std::vector<int> key(items.size());
   std::vector<long long> size(items.size());
   for (size_t k = 0; k < items.size(); ++k) {
@@ -231,6 +334,11 @@ qc_status qc_batch_create(qc_ctx* ctx, const qc_problem* problems, int32_t n_pro
     const long long smp = (it.r_hi - it.r_lo) * (long long)(it.c_hi - it.c_lo);
     size[k] = smp * (b->probs[it.prob].term.kind == KIND_C2X2 ? 2 : 1);
     key[k] = width_class(it.c_hi - it.c_lo) * N_SIZE + (smp < SMALL_SAMPLES ? 0 : 1);
+    if (team[k]) {
+      b->bucket[key[k]].team++;
+      b->n_team++;
+      key[k] = -1;
+    }
   }
   std::vector<size_t> order(items.size());
   std::iota(order.begin(), order.end(), 0);
@@ -239,7 +347,7 @@ qc_status qc_batch_create(qc_ctx* ctx, const qc_problem* problems, int32_t n_pro
   });
   std::vector<BatchItem> sorted(items.size());
   for (size_t k = 0; k < order.size(); ++k) sorted[k] = items[order[k]];
-  for (size_t k = 0; k < order.size(); ++k) {
+  for (size_t k = b->n_team; k < order.size(); ++k) {
     Bucket& bk = b->bucket[key[order[k]]];
     if (bk.count == 0) bk.begin = (int)k;
     bk.count++;
@@ -248,9 +356,14 @@ qc_status qc_batch_create(qc_ctx* ctx, const qc_problem* problems, int32_t n_pro
   int dev_cu = 0;
   HIP_TRY(ctx, hipDeviceGetAttribute(&dev_cu, hipDeviceAttributeMultiprocessorCount, ctx->device));
   b->n_cu = std::max(dev_cu, 1);
+  // 4 rows per step in every bucket (as the single-term solve), 8 wavefronts per
+  // workgroup where the intervals do not fill the chip several times over: on
+  // batches of 10 to 96 problems the autotuner took these for all but one
+  // bucket, and the graph went from 50.0 to 25.0 ms (24 problems) against 2 or 4
+  // wavefronts and 4, 2 or 1 rows by width
   for (int i = 0; i < N_BUCKET; ++i) {
-    const int w = i / N_SIZE, z = i % N_SIZE;
-    qc_status st = bucket_config(b, b->bucket[i], z == 0 ? 2 : 4, w == 0 ? 4 : (w == 1 ? 2 : 1));
+    qc_status st = bucket_config(b, b->bucket[i], b->bucket[i].count >= 8 * b->n_cu ? 4 : 8, 4);
+    if (st != QC_OK && b->bucket[i].count < 8 * b->n_cu) st = bucket_config(b, b->bucket[i], 4, 4);
     if (st != QC_OK) return bail(st);
   }
   if (hipMalloc(reinterpret_cast<void**>(&b->d_probs), sizeof(BatchProb) * b->probs.size()) != hipSuccess ||
@@ -261,16 +374,18 @@ qc_status qc_batch_create(qc_ctx* ctx, const qc_problem* problems, int32_t n_pro
   HIP_TRY(ctx, hipMemcpy(b->d_probs, b->probs.data(), sizeof(BatchProb) * b->probs.size(), hipMemcpyHostToDevice));
   if (!sorted.empty())
     HIP_TRY(ctx, hipMemcpy(b->d_items, sorted.data(), sizeof(BatchItem) * sorted.size(), hipMemcpyHostToDevice));
+  qc_status st = make_team(b, sorted);
+  if (st != QC_OK) return bail(st);
   if (hipStreamCreateWithFlags(&b->cs, hipStreamNonBlocking) != hipSuccess)
     return bail(fail(ctx, QC_E_DEVICE, "stream"));
-  for (int i = 0; i < N_BUCKET; ++i)
+  for (int i = 0; i <= N_BUCKET; ++i)
     if (hipStreamCreateWithFlags(&b->bs[i], hipStreamNonBlocking) != hipSuccess ||
         hipEventCreateWithFlags(&b->join[i], hipEventDisableTiming) != hipSuccess)
       return bail(fail(ctx, QC_E_DEVICE, "stream"));
   if (hipEventCreateWithFlags(&b->fork, hipEventDisableTiming) != hipSuccess || hipEventCreate(&b->t0) != hipSuccess ||
       hipEventCreate(&b->t1) != hipSuccess)
     return bail(fail(ctx, QC_E_DEVICE, "event"));
-  qc_status st = build_graph(b);
+  st = build_graph(b);
   if (st != QC_OK) return bail(st);
   *out = b;
   return QC_OK;
@@ -400,6 +515,19 @@ qc_status qc_batch_tune(qc_batch* b, int32_t reps) {
     }
     if (st == QC_OK && e == hipSuccess) bk = best;
   }
+  // the teams' launch has no choices; its time stands for the buckets whose
+  // intervals are all theirs
+  if (b->n_team > 0 && st == QC_OK && e == hipSuccess) {
+    e = copy_all(false);
+    if (e == hipSuccess) e = hipEventRecord(b->t0, b->cs);
+    if (e == hipSuccess) st = launch_team(b, b->cs);
+    if (e == hipSuccess) e = hipEventRecord(b->t1, b->cs);
+    if (e == hipSuccess) e = hipEventSynchronize(b->t1);
+    float ms = 0.f;
+    if (e == hipSuccess) e = hipEventElapsedTime(&ms, b->t0, b->t1);
+    for (Bucket& bk : b->bucket)
+      if (bk.count == 0 && bk.team > 0) bk.ms = ms;
+  }
   if (e == hipSuccess) e = copy_all(false);
   if (e == hipSuccess) e = hipStreamSynchronize(b->cs);
   hipFree(snap);
@@ -412,7 +540,7 @@ qc_status qc_batch_schedule(const qc_batch* b, int32_t* items, int32_t* waves, i
                             float* tuned_ms, int32_t n) {
   if (!b || n < N_BUCKET) return QC_E_ARG;
   for (int i = 0; i < N_BUCKET; ++i) {
-    if (items) items[i] = b->bucket[i].count;
+    if (items) items[i] = b->bucket[i].count + b->bucket[i].team;
     if (waves) waves[i] = b->bucket[i].waves;
     if (rows_per_step) rows_per_step[i] = b->bucket[i].rps;
     if (tuned_ms) tuned_ms[i] = b->bucket[i].ms;
@@ -428,7 +556,11 @@ qc_status qc_batch_destroy(qc_batch* b) {
   hipFree(b->d_probs);
   hipFree(b->d_items);
   hipFree(b->d_queue);
-  for (int i = 0; i < N_BUCKET; ++i) {
+  hipFree(b->d_team);
+  hipFree(b->d_team_words);
+  hipFree(b->d_team_parts);
+  hipFree(b->d_team_dv);
+  for (int i = 0; i <= N_BUCKET; ++i) {
     if (b->bs[i]) hipStreamDestroy(b->bs[i]);
     if (b->join[i]) hipEventDestroy(b->join[i]);
   }

@@ -943,6 +943,43 @@ __device__ __forceinline__ double band_top(const double* red) {
   return m;
 }
 
+// Values that workgroups of one launch hand to each other (AGENT: the batch's
+// teams): read and written past the caches that are not coherent between the
+// chip's dies, so that no cache has to be written back or invalidated as a
+// whole.  team_release orders a workgroup's writes before a flag that its
+// thread sets afterwards: every write has reached the coherent level.
+template <bool AGENT, typename X>
+__device__ __forceinline__ X ld_shared(const X* p) {
+  if constexpr (AGENT) return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  else return *p;
+}
+template <bool AGENT, typename X>
+__device__ __forceinline__ void st_shared(X* p, X x) {
+  if constexpr (AGENT) __hip_atomic_store(p, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  else *p = x;
+}
+template <bool AGENT>
+__device__ __forceinline__ double2 ld_shared2(const double2* p) {
+  const double* d = reinterpret_cast<const double*>(p);
+  if constexpr (AGENT) return make_double2(ld_shared<true>(d), ld_shared<true>(d + 1));
+  else return *p;
+}
+template <bool AGENT>
+__device__ __forceinline__ void st_shared2(double2* p, double2 x) {
+  double* d = reinterpret_cast<double*>(p);
+  if constexpr (AGENT) {
+    st_shared<true>(d, x.x);
+    st_shared<true>(d + 1, x.y);
+  } else {
+    *p = x;
+  }
+}
+__device__ __forceinline__ void team_release() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+  __builtin_amdgcn_s_waitcnt(0);
+  __syncthreads();
+}
+
 // LDS bytes the interval solve needs for n_ant antennas and nw waves.
 // lane_rows: steps of one row per lane, which add a claim word per antenna
 // and wave.
@@ -1234,6 +1271,9 @@ __device__ __forceinline__ bool update_and_test(const Sum& sum, double2* gm, cx<
 //         J.gains; the FP64 blocks and chi^2 go to J.partial (split schedule).
 // LMT:    Levenberg-Marquardt damping (kernels of their own, so that the
 //         Gauss-Newton kernels carry none of its state).
+// RST:    1: an interval whose start is worse than its reference returns at
+//         once (the batch's warm kernel); 2: a part of a team's pass, whose
+//         gains and block other workgroups write and read.
 // SKY:    the model of each sample is predicted from J.sky's point components
 //         (a direct Fourier sum per direction) instead of read from the
 //         visibility set: single-term and diagonal-chain evaluation.
@@ -1328,7 +1368,7 @@ __device__ __forceinline__ void solve_interval(const Job& J) {
     } else {
 #pragma unroll
       for (int k = 0; k < 4; ++k) {
-        const double2 g = J.gains[4 * src + k];
+        const double2 g = ld_shared2<RST == 2>(J.gains + 4 * src + k);
         gm[slot * 4 + k] = g;
         gc[slot * 4 + k] = cmake<T>((T)g.x, (T)g.y);
       }
@@ -2017,8 +2057,8 @@ __device__ __forceinline__ void solve_interval(const Job& J) {
     double chi_now = 0.0;
     for (int w = 0; w < nw; ++w) chi_now += chiw[w];
     if constexpr (PASS_ONLY) {
-      for (int i = threadIdx.x; i < slot_vals; i += blockDim.x) J.partial[i] = slot_sum(i);
-      if (threadIdx.x == 0) J.partial[slot_vals] = chi_now;
+      for (int i = threadIdx.x; i < slot_vals; i += blockDim.x) st_shared<RST == 2>(J.partial + i, slot_sum(i));
+      if (threadIdx.x == 0) st_shared<RST == 2>(J.partial + slot_vals, chi_now);
       __syncthreads();
       return;
     }
@@ -2255,18 +2295,28 @@ __device__ __forceinline__ void split_update_lm(const Job& J, const double* tot,
   }
 }
 
+// Where a team's update keeps its divergence state: after the update's LDS.
+template <int KIND, typename T>
+__host__ __device__ constexpr size_t team_dv_off(int n_ant) {
+  return (interval_lds_bytes<KIND, T, 1>(n_ant, 0) + 15) & ~size_t(15);
+}
+
 // Sums the interval's n_part partial blocks in a fixed order, then does what
-// the fused loop does after a pass: chi^2 bookkeeping, the FP64 block solves,
-// the damped update of the gains in device memory, the convergence test.
-template <int KIND, typename T, int NG, bool FB = false>
-__device__ __forceinline__ void split_update(const Job& J, const double* partials, int n_part, const SplitState& St) {
+// the fused loop does after pass `pass`: chi^2 bookkeeping, the FP64 block
+// solves, the damped update of the gains in device memory (dv: the interval's
+// divergence state), the convergence test.  Returns whether the interval is
+// done.  TEAM: the parts come from the same launch (the batch's team kernel;
+// no Levenberg-Marquardt).
+template <int KIND, typename T, int NG, bool FB = false, bool TEAM = false>
+__device__ __forceinline__ bool split_update_at(const Job& J, const double* partials, int n_part, double* dv, int pass,
+                                                const SplitState* St) {
   constexpr int NV = nv_of<KIND, FB>();
   const VisArgs& V = *J.V;
   const TermArgs& TA = *J.TA;
   const int n_ant = V.n_ant;
   const int n_gdir = TA.n_gdir;
   const int interval = J.gt * J.n_gf + J.gf;
-  if (St.done[interval]) return;
+  double* dv_mem = nullptr;
   const int n_slots = n_ant * NG;
   const int slot_vals = n_slots * NV;
   unsigned char* lp = qc_lds;
@@ -2277,6 +2327,12 @@ __device__ __forceinline__ void split_update(const Job& J, const double* partial
   cx<T>* gc = reinterpret_cast<cx<T>*>(lp);               lp += sizeof(cx<T>) * n_slots * 4;
   int* gfl = reinterpret_cast<int*>(lp);                  lp += sizeof(int) * n_slots;
   int* ctl = reinterpret_cast<int*>(lp);
+  if constexpr (TEAM) {                          // the divergence state, in LDS during the update
+    double* dl = reinterpret_cast<double*>(qc_lds + team_dv_off<KIND, T>(n_ant));
+    for (int i = threadIdx.x; i < 2 * n_slots; i += blockDim.x) dl[i] = pass > 0 ? ld_shared<true>(dv + i) : 0.0;
+    dv_mem = dv;
+    dv = dl;
+  }
   const size_t gbase = ((size_t)J.gt * J.n_gf + J.gf) * n_ant;
   for (int i = threadIdx.x; i < n_ant * n_gdir; i += blockDim.x) {
     const int ant = i / n_gdir, gd = i - ant * n_gdir;
@@ -2287,7 +2343,7 @@ __device__ __forceinline__ void split_update(const Job& J, const double* partial
     } else {
 #pragma unroll
       for (int k = 0; k < 4; ++k) {
-        const double2 g = J.gains[4 * src + k];
+        const double2 g = ld_shared2<TEAM>(J.gains + 4 * src + k);
         gm[slot * 4 + k] = g;
         gc[slot * 4 + k] = cmake<T>((T)g.x, (T)g.y);
       }
@@ -2297,12 +2353,12 @@ __device__ __forceinline__ void split_update(const Job& J, const double* partial
   const size_t stride = (size_t)slot_vals + 1;
   for (int i = threadIdx.x; i < slot_vals; i += blockDim.x) {
     double sum = 0.0;
-    for (int k = 0; k < n_part; ++k) sum += partials[k * stride + i];
+    for (int k = 0; k < n_part; ++k) sum += ld_shared<TEAM>(partials + k * stride + i);
     tot[i] = sum;
   }
   if (threadIdx.x == 0) {
     double c = 0.0;
-    for (int k = 0; k < n_part; ++k) c += partials[k * stride + slot_vals];
+    for (int k = 0; k < n_part; ++k) c += ld_shared<TEAM>(partials + k * stride + slot_vals);
     chiw[0] = c;
   }
   if constexpr (is_param(KIND)) band_top_part(V, J.c_lo, J.c_hi, red);
@@ -2310,22 +2366,22 @@ __device__ __forceinline__ void split_update(const Job& J, const double* partial
   const double chi_now = chiw[0];
   double nu_max = 0.0;
   if constexpr (is_param(KIND)) nu_max = band_top(red);
-  const int pass = St.passes[interval];
   if (threadIdx.x == 0) {
-    if (pass == 0 && J.chisq_first) J.chisq_first[interval] = chi_now;
-    if (J.chisq_last) J.chisq_last[interval] = chi_now;
+    if (pass == 0 && J.chisq_first) st_shared<TEAM>(J.chisq_first + interval, chi_now);
+    if (J.chisq_last) st_shared<TEAM>(J.chisq_last + interval, chi_now);
   }
   __syncthreads();
-  if (J.damping == DAMP_LM) {
-    split_update_lm<KIND, T, NG, FB>(J, tot, gm, gc, gfl, red, ctl, chi_now, nu_max, pass, St);
-    return;
+  if constexpr (!TEAM) {
+    if (J.damping == DAMP_LM) {
+      split_update_lm<KIND, T, NG, FB>(J, tot, gm, gc, gfl, red, ctl, chi_now, nu_max, pass, *St);
+      return false;                             // (its intervals finish there)
+    }
   }
   bool finish = false, conv = false;
   if (pass >= J.max_iter) {
     finish = true;
   } else {
     const int k_upd = pass + 1;
-    double* dv = St.dv + (size_t)interval * n_slots * 2;
     conv = update_and_test<KIND, T, NG, FB>([&](size_t i) -> double { return tot[i]; }, gm, gc, gfl, dv, red,
                                             ctl, n_ant, n_gdir, k_upd, J.damping, nu_max, J.tol, J.err, J.TA->kind);
     finish = conv || k_upd >= J.max_iter;
@@ -2337,21 +2393,41 @@ __device__ __forceinline__ void split_update(const Job& J, const double* partial
         params_store<KIND>(J.params, dst, gm + slot * 4);
       } else {
 #pragma unroll
-        for (int k = 0; k < 4; ++k) J.gains[4 * dst + k] = gm[slot * 4 + k];
+        for (int k = 0; k < 4; ++k) st_shared2<TEAM>(J.gains + 4 * dst + k, gm[slot * 4 + k]);
       }
       if (J.gflags) {
         int f = gfl[slot];
         if (f == 0 && finish && !conv && dv[2 * slot] >= (double)DIV_RUN) f = 2;   // updates did not tend to zero
-        J.gflags[dst] = (int8_t)f;
+        st_shared<TEAM>(J.gflags + dst, (int8_t)f);
       }
+    }
+  }
+  if constexpr (TEAM) {
+    for (int i = threadIdx.x; i < n_ant * n_gdir; i += blockDim.x) {      // the thread's own blocks
+      st_shared<true>(dv_mem + 2 * i, dv[2 * i]);
+      st_shared<true>(dv_mem + 2 * i + 1, dv[2 * i + 1]);
     }
   }
   if (threadIdx.x == 0) {
     const int iters = pass >= J.max_iter ? pass : pass + 1;
+    if (J.iters) st_shared<TEAM>(J.iters + interval, iters);
+    if (J.converged) st_shared<TEAM>(J.converged + interval, (uint8_t)(conv ? 1 : 0));
+    if (J.restarted) st_shared<TEAM>(J.restarted + interval, (uint8_t)0);
+  }
+  return finish;
+}
+
+// The update of an interval by a launch of its own (k_split_update).
+template <int KIND, typename T, int NG, bool FB = false>
+__device__ __forceinline__ void split_update(const Job& J, const double* partials, int n_part, const SplitState& St) {
+  const int interval = J.gt * J.n_gf + J.gf;
+  if (St.done[interval]) return;
+  const int pass = St.passes[interval];
+  double* dv = St.dv + (size_t)interval * J.V->n_ant * NG * 2;
+  const bool finish = split_update_at<KIND, T, NG, FB>(J, partials, n_part, dv, pass, &St);
+  if (J.damping == DAMP_LM) return;
+  if (threadIdx.x == 0) {
     St.passes[interval] = pass + 1;
-    if (J.iters) J.iters[interval] = iters;
-    if (J.converged) J.converged[interval] = conv ? 1 : 0;
-    if (J.restarted) J.restarted[interval] = 0;
     if (finish) split_finish(St, interval);
   }
 }
