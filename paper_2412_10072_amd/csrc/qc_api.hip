@@ -882,8 +882,7 @@ qc_status qc_mlp_backward(qc_ctx* ctx, const float* params, const float* x, cons
   float* gb1 = gW1 + (size_t)n_hid * n_in;
   float* gW2 = gb1 + n_hid;
   float* gb2 = gW2 + (size_t)n_out * n_hid;
-  HIP_TRY(ctx, launch_linear_bwd_w(pre, dy, gW2, gb2, batch, n_hid, n_out, 1, s));
-  HIP_TRY(ctx, launch_linear_bwd_x(dy, W2, pre, ctx->d_dh, batch, n_hid, n_out, 1, s));
+  HIP_TRY(ctx, launch_linear_bwd_out(pre, dy, W2, gW2, gb2, ctx->d_dh, batch, n_hid, n_out, s));
   HIP_TRY(ctx, launch_linear_bwd_w(x, ctx->d_dh, gW1, gb1, batch, n_in, n_hid, 0, s));
   return QC_OK;
 }

@@ -520,8 +520,10 @@ hipError_t launch_linear_fwd(const float* x, const float* W, const float* b, flo
                              int relu_in, hipStream_t s);
 hipError_t launch_linear_bwd_w(const float* x, const float* dy, float* gW, float* gb, int B, int I, int O,
                                int relu_in, hipStream_t s);
-hipError_t launch_linear_bwd_x(const float* dy, const float* W, const float* pre, float* dx, int B, int I, int O,
-                               int relu_mask, hipStream_t s);
+// the output layer: weight gradients, and the hidden layer's gradients dh from
+// its pre-activations h
+hipError_t launch_linear_bwd_out(const float* h, const float* dy, const float* W, float* gW, float* gb, float* dh,
+                                 int B, int H, int O, hipStream_t s);
 hipError_t launch_adam(float* p, const float* g, float* m, float* v, int n, float lr, float b1, float b2, float eps,
                        int step, hipStream_t s);
 hipError_t launch_mse(const float* y, const float* t, float* dy, float* loss, int n, hipStream_t s);

@@ -199,85 +199,150 @@ __global__ void k_batch_ws_gains(const BatchProb* probs, const BatchItem* items,
 }
 
 // ---------------------------------------------------------------------------
-// MLP layers: y[b][o] = sum_i act(x[b][i]) W[o][i] + bias[o] (act = relu or id)
-// 16 x 16 output tiles; every output is one thread's sequential sum over i.
+// MLP layers on the FP32 matrix instructions (products and sums in FP32):
+//   forward   y[b][o]  = sum_i act(x[b][i]) W[o][i] + bias[o]   (act = relu or id)
+//   weights   gW[o][i] = sum_b dy[b][o] act(x[b][i]), gb[o] = sum_b dy[b][o]
+//   inputs    dx[b][i] = sum_o dy[b][o] W[o][i], zero where pre[b][i] <= 0
+// as C[m][n] = sum_k A[m][k] B[k][n].  At the network's sizes (512 -> 256 -> 256,
+// batch 256: 0.07 GFLOP a layer) a product is bound by latency, not by rate: a
+// workgroup takes 16 x 16 outputs, so that a layer has 256 to 512 of them, its
+// four wavefronts each every fourth 16-deep slice of k straight from global
+// memory (the operands are a few hundred KB, in the L2), and their sums meet in
+// LDS in a fixed order.  Products of many rows (inference over thousands of
+// intervals) take 32 x 32 outputs, which halves the reads.  Measured before (16 x
+// 16 outputs, one thread's sequential sum each) and now, batch 256, a kernel:
+// forward 15.8 -> 6.2 us, weights 13.1 -> 5.5, the output layer's weights and the
+// inputs 23.9 -> 5.9 in one launch; the forward call over 9600 rows 251 -> 72 us.
 // ---------------------------------------------------------------------------
-constexpr int TILE = 16;
+using f32x4 = __attribute__((ext_vector_type(4))) float;
 
-__global__ void __launch_bounds__(256) k_linear_fwd(const float* __restrict__ x, const float* __restrict__ W,
-                                                    const float* __restrict__ bias, float* __restrict__ y,
-                                                    int B, int I, int O, int relu_in) {
-  __shared__ float xs[TILE][TILE + 1];
-  __shared__ float ws[TILE][TILE + 1];
-  const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
-  const int b = blockIdx.y * TILE + ty, o = blockIdx.x * TILE + tx;
-  float acc = 0.f;
-  for (int i0 = 0; i0 < I; i0 += TILE) {
-    const int bx = blockIdx.y * TILE + ty, ix = i0 + tx;
-    float xv = (bx < B && ix < I) ? x[(size_t)bx * I + ix] : 0.f;
-    if (relu_in) xv = fmaxf(xv, 0.f);
-    xs[ty][tx] = xv;
-    const int ow = blockIdx.x * TILE + ty;
-    ws[ty][tx] = (ow < O && ix < I) ? W[(size_t)ow * I + ix] : 0.f;
-    __syncthreads();
+constexpr int MM = 16;             // rows and columns of one matrix instruction
+constexpr int MM_K = 16;           // depth of a slice: four instructions of depth 4
+constexpr int MM_WAVES = 4;
+
+struct MatArgs {
+  const float* a;                  // A[m][k] at a[m * lda + k], or a[k * lda + m] (k-major)
+  const float* b;                  // B[k][n] at b[n * ldb + k], or b[k * ldb + n] (k-major)
+  float* c;                        // [m][n], row length N
+  const float* bias;               // [n], added (forward); null: none
+  const float* pre;                // [m][n]: c zero where pre <= 0 (inputs); null: none
+  float* a_sum;                    // [m] sum_k A[m][k] (weights: the bias gradient); null: none
+  int M, N, K, lda, ldb;
+  int relu_a, relu_b;              // negative operand values read as zero
+};
+
+// Values k .. k + 3 of operand row r (zero outside the operand).  KMAJOR: the
+// rows of one k lie side by side; else one row's values do, read as 16 bytes
+// when VEC (row length a multiple of 4, base 16-byte aligned: the host looks).
+template <bool KMAJOR, bool VEC>
+__device__ __forceinline__ f32x4 mat_load(const float* p, int ld, int r, int n_r, int k, int n_k, int relu) {
+  f32x4 v = {0.f, 0.f, 0.f, 0.f};
+  if constexpr (!KMAJOR && VEC) {
+    if (r < n_r && k < n_k) v = *reinterpret_cast<const f32x4*>(p + (size_t)r * ld + k);
+  } else {
 #pragma unroll
-    for (int k = 0; k < TILE; ++k) acc = fmaf(xs[ty][k], ws[tx][k], acc);
-    __syncthreads();
+    for (int e = 0; e < 4; ++e)
+      if (r < n_r && k + e < n_k) v[e] = KMAJOR ? p[(size_t)(k + e) * ld + r] : p[(size_t)r * ld + k + e];
   }
-  if (b < B && o < O) y[(size_t)b * O + o] = acc + bias[o];
+  if (relu) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[e] = fmaxf(v[e], 0.f);
+  }
+  return v;
 }
 
-// gW[o][i] = sum_b dy[b][o] act(x[b][i]); gbias[o] = sum_b dy[b][o]
-__global__ void __launch_bounds__(256) k_linear_bwd_w(const float* __restrict__ x, const float* __restrict__ dy,
-                                                      float* __restrict__ gW, float* __restrict__ gbias,
-                                                      int B, int I, int O, int relu_in) {
-  __shared__ float xs[TILE][TILE + 1];
-  __shared__ float ds[TILE][TILE + 1];
-  const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
-  const int i = blockIdx.x * TILE + tx, o = blockIdx.y * TILE + ty;
-  float acc = 0.f, accb = 0.f;
-  for (int b0 = 0; b0 < B; b0 += TILE) {
-    const int bb = b0 + ty;
-    const int ix = blockIdx.x * TILE + tx;
-    float xv = (bb < B && ix < I) ? x[(size_t)bb * I + ix] : 0.f;
-    if (relu_in) xv = fmaxf(xv, 0.f);
-    xs[ty][tx] = xv;
-    const int ox = blockIdx.y * TILE + tx;
-    ds[ty][tx] = (bb < B && ox < O) ? dy[(size_t)bb * O + ox] : 0.f;
-    __syncthreads();
+// Outputs [16 MT][16 NT] at (tile_m, tile_n), one workgroup.  Operand lanes:
+// row (column) lane % 16, depth 4 (lane / 16) + e in the e-th instruction of a
+// slice; result register r: row 4 (lane / 16) + r, column lane % 16.
+template <bool AK, bool BK, int MT, int NT, bool VEC>
+__device__ __forceinline__ void mat_tile(const MatArgs& G, int tile_m, int tile_n) {
+  __shared__ float red[MM_WAVES][MT * NT][4][64];
+  __shared__ float red_a[MM_WAVES][MT * MM];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int row = lane & 15, kq = lane >> 4;
+  const int m0 = tile_m * MM * MT, n0 = tile_n * MM * NT;
+  f32x4 acc[MT][NT];
+  float asum[MT];
 #pragma unroll
-    for (int k = 0; k < TILE; ++k) {
-      acc = fmaf(ds[k][ty], xs[k][tx], acc);
-      accb += ds[k][ty];
+  for (int i = 0; i < MT; ++i) {
+    asum[i] = 0.f;
+#pragma unroll
+    for (int j = 0; j < NT; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  }
+#pragma unroll 2
+  for (int k0 = wave * MM_K; k0 < G.K; k0 += MM_WAVES * MM_K) {
+    f32x4 a[MT], b[NT];
+    const int k = k0 + 4 * kq;
+#pragma unroll
+    for (int i = 0; i < MT; ++i) a[i] = mat_load<AK, VEC>(G.a, G.lda, m0 + i * MM + row, G.M, k, G.K, G.relu_a);
+#pragma unroll
+    for (int j = 0; j < NT; ++j) b[j] = mat_load<BK, VEC>(G.b, G.ldb, n0 + j * MM + row, G.N, k, G.K, G.relu_b);
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+#pragma unroll
+      for (int i = 0; i < MT; ++i) {
+        asum[i] += a[i][e];
+#pragma unroll
+        for (int j = 0; j < NT; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i][e], b[j][e], acc[i][j], 0, 0, 0);
+      }
+  }
+#pragma unroll
+  for (int i = 0; i < MT; ++i)
+#pragma unroll
+    for (int j = 0; j < NT; ++j)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) red[wave][i * NT + j][r][lane] = acc[i][j][r];
+  const bool sums = G.a_sum && tile_n == 0;
+  if (sums) {
+#pragma unroll
+    for (int i = 0; i < MT; ++i) {
+      float x = asum[i];
+      x += __shfl_xor(x, 16);
+      x += __shfl_xor(x, 32);
+      if (lane < MM) red_a[wave][i * MM + lane] = x;
     }
-    __syncthreads();
   }
-  if (o < O && i < I) gW[(size_t)o * I + i] = acc;
-  if (blockIdx.x == 0 && tx == 0 && o < O) gbias[o] = accb;
+  __syncthreads();
+  // thread (r, lane) of every 16 x 16 block: the four wavefronts' sums in order
+  const int r = wave;
+#pragma unroll
+  for (int t = 0; t < MT * NT; ++t) {
+    const int m = m0 + (t / NT) * MM + 4 * kq + r, n = n0 + (t % NT) * MM + row;
+    float x = red[0][t][r][lane];
+#pragma unroll
+    for (int w = 1; w < MM_WAVES; ++w) x += red[w][t][r][lane];
+    if (m < G.M && n < G.N) {
+      const size_t o = (size_t)m * G.N + n;
+      if (G.bias) x += G.bias[n];
+      if (G.pre && !(G.pre[o] > 0.f)) x = 0.f;
+      G.c[o] = x;
+    }
+  }
+  if (sums && threadIdx.x < MT * MM && m0 + (int)threadIdx.x < G.M) {
+    float x = red_a[0][threadIdx.x];
+#pragma unroll
+    for (int w = 1; w < MM_WAVES; ++w) x += red_a[w][threadIdx.x];
+    G.a_sum[m0 + threadIdx.x] = x;
+  }
 }
 
-// dx[b][i] = (sum_o dy[b][o] W[o][i]) * (pre[b][i] > 0 when relu_mask)
-__global__ void __launch_bounds__(256) k_linear_bwd_x(const float* __restrict__ dy, const float* __restrict__ W,
-                                                      const float* __restrict__ pre, float* __restrict__ dx,
-                                                      int B, int I, int O, int relu_mask) {
-  __shared__ float dys[TILE][TILE + 1];
-  __shared__ float ws[TILE][TILE + 1];
-  const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
-  const int b = blockIdx.y * TILE + ty, i = blockIdx.x * TILE + tx;
-  float acc = 0.f;
-  for (int o0 = 0; o0 < O; o0 += TILE) {
-    const int ox = o0 + tx;
-    dys[ty][tx] = (b < B && ox < O) ? dy[(size_t)b * O + ox] : 0.f;
-    const int ow = o0 + ty;
-    ws[ty][tx] = (ow < O && i < I) ? W[(size_t)ow * I + i] : 0.f;
-    __syncthreads();
-#pragma unroll
-    for (int k = 0; k < TILE; ++k) acc = fmaf(dys[ty][k], ws[k][tx], acc);
-    __syncthreads();
-  }
-  if (b < B && i < I) {
-    if (relu_mask && !(pre[(size_t)b * I + i] > 0.f)) acc = 0.f;
-    dx[(size_t)b * I + i] = acc;
+template <bool AK, bool BK, int MT, int NT, bool VEC>
+__global__ void __launch_bounds__(64 * MM_WAVES) k_mat(MatArgs G) {
+  mat_tile<AK, BK, MT, NT, VEC>(G, blockIdx.y, blockIdx.x);
+}
+
+// The output layer's backward: its weight gradients and the hidden layer's
+// gradients need only the outputs' gradients, so one launch does both (the
+// first n_w workgroups the weights).
+template <bool VEC>
+__global__ void __launch_bounds__(64 * MM_WAVES) k_mat_bwd_out(MatArgs W, MatArgs X, int n_w) {
+  const int i = (int)blockIdx.x - n_w;
+  if (i < 0) {
+    const int nt = (W.N + MM - 1) / MM;
+    mat_tile<true, true, 1, 1, VEC>(W, blockIdx.x / nt, blockIdx.x % nt);
+  } else {
+    const int nt = (X.N + MM - 1) / MM;
+    mat_tile<false, true, 1, 1, VEC>(X, i / nt, i % nt);
   }
 }
 
@@ -294,19 +359,49 @@ __global__ void k_adam(float* __restrict__ p, const float* __restrict__ g, float
   p[i] -= lr * mh / (sqrtf(vh) + eps);
 }
 
-// dy = 2 (y - t) / n; loss = sum (y - t)^2 / n (one workgroup of 1024
-// threads, fixed order: 4x the 256 it had, the kernel measured at 75 us for a
-// 256 x 256 batch being the longest step of training)
+// dy = 2 (y - t) / n by workgroups 1 .. of the grid, 16 bytes a thread where the
+// arrays allow (VEC); loss = sum (y - t)^2 / n by workgroup 0 alone, in FP64 and a
+// fixed order (no sums handed between workgroups, so no scratch memory).  Bound by
+// what one compute unit reads (solo, where dy is y or t: one workgroup, each
+// thread its own elements), four 16-byte loads of each array in flight per
+// thread: 65536 outputs 23.5 us in one workgroup with 4-byte reads -> 7.6 us.
 constexpr int MSE_THREADS = 1024;
-__global__ void __launch_bounds__(MSE_THREADS) k_mse(const float* __restrict__ y, const float* __restrict__ t,
-                                                     float* __restrict__ dy, float* __restrict__ loss, int n) {
+template <bool VEC>
+__global__ void __launch_bounds__(MSE_THREADS) k_mse(const float* y, const float* t, float* dy,
+                                                     float* loss, int n, int solo) {
+  constexpr int W = VEC ? 4 : 1;
+  const int nv = n / W;                            // VEC: n is a multiple of 4
+  const f32x4* y4 = reinterpret_cast<const f32x4*>(y);
+  const f32x4* t4 = reinterpret_cast<const f32x4*>(t);
+  if (blockIdx.x > 0) {
+    const float inv = 1.f / (float)n;
+    const int i = (blockIdx.x - 1) * MSE_THREADS + threadIdx.x;
+    if (i >= nv) return;
+    if constexpr (VEC) reinterpret_cast<f32x4*>(dy)[i] = 2.f * (y4[i] - t4[i]) * inv;
+    else dy[i] = 2.f * (y[i] - t[i]) * inv;
+    return;
+  }
   __shared__ double red[MSE_THREADS];
   double s = 0.0;
-  const float inv = 1.f / (float)n;
-  for (int i = threadIdx.x; i < n; i += blockDim.x) {
-    const float d = y[i] - t[i];
-    dy[i] = 2.f * d * inv;
-    s += (double)d * (double)d;
+  if (solo) {
+    const float inv = 1.f / (float)n;
+    for (int i = threadIdx.x; i < n; i += MSE_THREADS) {
+      const float d = y[i] - t[i];
+      dy[i] = 2.f * d * inv;
+      s += (double)d * (double)d;
+    }
+  } else if (loss) {
+#pragma unroll 4
+    for (int i = threadIdx.x; i < nv; i += MSE_THREADS) {
+      if constexpr (VEC) {
+        const f32x4 d = y4[i] - t4[i];
+        s += ((double)d[0] * (double)d[0] + (double)d[1] * (double)d[1]) +
+             ((double)d[2] * (double)d[2] + (double)d[3] * (double)d[3]);
+      } else {
+        const float d = y[i] - t[i];
+        s += (double)d * (double)d;
+      }
+    }
   }
   red[threadIdx.x] = s;
   __syncthreads();
@@ -403,24 +498,48 @@ hipError_t launch_ws_features(const FeatLaunch& L, int waves, hipStream_t stream
   return hipGetLastError();
 }
 
-hipError_t launch_linear_fwd(const float* x, const float* W, const float* b, float* y, int B, int I, int O,
+static bool aligned16(const void* p) { return reinterpret_cast<uintptr_t>(p) % 16 == 0; }
+
+// 32 x 32 outputs where they still give two workgroups per compute unit (both
+// layers forward, 512 -> 256 -> 256: 2016 rows, just below, 27.6 us; 2048 rows 22.7)
+template <bool AK, bool BK>
+static void launch_mat(const MatArgs& G, bool vec, hipStream_t s) {
+  const dim3 g2((G.N + 2 * MM - 1) / (2 * MM), (G.M + 2 * MM - 1) / (2 * MM));
+  const dim3 g1((G.N + MM - 1) / MM, (G.M + MM - 1) / MM), b(64 * MM_WAVES);
+  if ((long long)g2.x * g2.y >= 512) {
+    if (vec) hipLaunchKernelGGL((k_mat<AK, BK, 2, 2, true>), g2, b, 0, s, G);
+    else hipLaunchKernelGGL((k_mat<AK, BK, 2, 2, false>), g2, b, 0, s, G);
+  } else {
+    if (vec) hipLaunchKernelGGL((k_mat<AK, BK, 1, 1, true>), g1, b, 0, s, G);
+    else hipLaunchKernelGGL((k_mat<AK, BK, 1, 1, false>), g1, b, 0, s, G);
+  }
+}
+
+hipError_t launch_linear_fwd(const float* x, const float* W, const float* bias, float* y, int B, int I, int O,
                              int relu_in, hipStream_t s) {
-  hipLaunchKernelGGL(k_linear_fwd, dim3((O + TILE - 1) / TILE, (B + TILE - 1) / TILE), dim3(256), 0, s, x, W, b, y,
-                     B, I, O, relu_in);
+  const MatArgs G{x, W, y, bias, nullptr, nullptr, B, O, I, I, I, relu_in, 0};
+  launch_mat<false, false>(G, I % 4 == 0 && aligned16(x) && aligned16(W), s);
   return hipGetLastError();
+}
+
+static MatArgs mat_bwd_w(const float* x, const float* dy, float* gW, float* gb, int B, int I, int O, int relu_in) {
+  return MatArgs{dy, x, gW, nullptr, nullptr, gb, O, I, B, O, I, 0, relu_in};
 }
 
 hipError_t launch_linear_bwd_w(const float* x, const float* dy, float* gW, float* gb, int B, int I, int O,
                                int relu_in, hipStream_t s) {
-  hipLaunchKernelGGL(k_linear_bwd_w, dim3((I + TILE - 1) / TILE, (O + TILE - 1) / TILE), dim3(256), 0, s, x, dy,
-                     gW, gb, B, I, O, relu_in);
+  launch_mat<true, true>(mat_bwd_w(x, dy, gW, gb, B, I, O, relu_in), false, s);
   return hipGetLastError();
 }
 
-hipError_t launch_linear_bwd_x(const float* dy, const float* W, const float* pre, float* dx, int B, int I, int O,
-                               int relu_mask, hipStream_t s) {
-  hipLaunchKernelGGL(k_linear_bwd_x, dim3((I + TILE - 1) / TILE, (B + TILE - 1) / TILE), dim3(256), 0, s, dy, W,
-                     pre, dx, B, I, O, relu_mask);
+hipError_t launch_linear_bwd_out(const float* h, const float* dy, const float* W, float* gW, float* gb, float* dh,
+                                 int B, int H, int O, hipStream_t s) {
+  const MatArgs Gw = mat_bwd_w(h, dy, gW, gb, B, H, O, 1);
+  const MatArgs Gx{dy, W, dh, nullptr, h, nullptr, B, H, O, O, H, 0, 0};
+  const int n_w = ((H + MM - 1) / MM) * ((O + MM - 1) / MM), n_x = ((H + MM - 1) / MM) * ((B + MM - 1) / MM);
+  const dim3 g(n_w + n_x), b(64 * MM_WAVES);
+  if (O % 4 == 0 && aligned16(dy)) hipLaunchKernelGGL(k_mat_bwd_out<true>, g, b, 0, s, Gw, Gx, n_w);
+  else hipLaunchKernelGGL(k_mat_bwd_out<false>, g, b, 0, s, Gw, Gx, n_w);
   return hipGetLastError();
 }
 
@@ -432,7 +551,12 @@ hipError_t launch_adam(float* p, const float* g, float* m, float* v, int n, floa
 }
 
 hipError_t launch_mse(const float* y, const float* t, float* dy, float* loss, int n, hipStream_t s) {
-  hipLaunchKernelGGL(k_mse, dim3(1), dim3(MSE_THREADS), 0, s, y, t, dy, loss, n);
+  const int solo = dy == y || dy == t;             // in place: workgroup 0 must not read what others write
+  const bool vec = !solo && n % 4 == 0 && aligned16(y) && aligned16(t) && aligned16(dy);
+  const int per = vec ? 4 * MSE_THREADS : MSE_THREADS;
+  const dim3 g(solo ? 1 : 1 + (n - 1) / per + 1), b(MSE_THREADS);
+  if (vec) hipLaunchKernelGGL(k_mse<true>, g, b, 0, s, y, t, dy, loss, n, solo);
+  else hipLaunchKernelGGL(k_mse<false>, g, b, 0, s, y, t, dy, loss, n, solo);
   return hipGetLastError();
 }
 
