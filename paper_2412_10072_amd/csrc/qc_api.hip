@@ -926,6 +926,49 @@ qc_status qc_ws_labels(qc_ctx* ctx, const void* gains, int32_t n_int, int32_t n_
   return QC_OK;
 }
 
+// Whether the outputs read the direction-independent chain from a table.  It
+// pays where a sample's chain takes more than one gain block that the wavefront's
+// lanes share: several such terms (residual of a K.B.G.dE chain over 4
+// directions, 64 antennas, 60 times x 256 channels: 1969 -> 1582 us), complex64
+// outputs through solutions narrower than 16 channels (one per channel, 40 x
+// 512: residual 1425 -> 826 us, CORRECT 1222 -> 623, weights 938 -> 387; their
+// FP64 blocks of 64 bytes lie one per lane), complex128 ones through phasors.  It
+// does not for one delay term in complex64 (CORRECT 1298 against 1398 us with a
+// table) nor for 32-channel solutions in complex128 (251 against 329 us), whose
+// entries are as long as the gain blocks.  The baselines must outnumber the
+// antennas enough to pay for it (four rows per time and antenna), and it stays
+// below OUT_TABLE_BYTES.  A full product is tabulated only where every term is
+// direction independent.
+constexpr size_t OUT_TABLE_BYTES = (size_t)1 << 30;
+static bool out_table_pays(const OutputLaunch& L, const qc_vis* vis, const qc_term* chain, int n_term,
+                           const std::vector<HostMaps>& maps) {
+  constexpr int NARROW = 16;
+  int di = 0;
+  bool costly = false;
+  for (int j = 0; j < n_term; ++j) {
+    if (L.chain.t[j].n_gdir > 1) {
+      if (!L.diag_chain) return false;
+      continue;
+    }
+    ++di;
+    if (L.vis_is_c128) {
+      if (chain[j].type != QC_TERM_DIAGONAL && chain[j].type != QC_TERM_COMPLEX2X2 &&
+          chain[j].type != QC_TERM_AMPLITUDE)
+        costly = true;
+    } else {
+      // (f_map does not decrease) a gain frequency of fewer than NARROW channels, but the last
+      int first = 0;
+      for (int c = 1; c < vis->n_chan && !costly; ++c) {
+        if (maps[j].f_map[c] == maps[j].f_map[c - 1]) continue;
+        costly = c - first < NARROW;
+        first = c;
+      }
+    }
+  }
+  if (di == 0 || !(costly || di > 1)) return false;
+  return vis->n_row >= 4LL * vis->n_time * vis->n_ant && out_table_bytes(L) <= OUT_TABLE_BYTES;
+}
+
 static qc_status outputs_common(qc_ctx* ctx, const qc_vis* vis, const qc_term* chain, int32_t n_term, int mode,
                                 const uint8_t* dir_mask, void* out, void* stream, const qc_sky* sky = nullptr,
                                 const double* uvw = nullptr) {
@@ -965,7 +1008,18 @@ static qc_status outputs_common(qc_ctx* ctx, const qc_vis* vis, const qc_term* c
   L.w_vec = mode == 3 && vis->n_wcorr == 4 && reinterpret_cast<uintptr_t>(vis->weight) % 16 == 0 &&
             reinterpret_cast<uintptr_t>(out) % 16 == 0;
   L.sky = sk;
+  L.tab = nullptr;
+  void* table = nullptr;
+  if (!sky && out_table_pays(L, vis, chain, n_term, maps)) {
+    const size_t bytes = out_table_bytes(L);
+    if (grow(ctx->d_otab, ctx->otab_cap, bytes) == hipSuccess) table = ctx->d_otab;
+    else (void)hipGetLastError();              // no memory for it: the chain is formed per sample
+  }
   HIP_TRY(ctx, hipEventRecord(ctx->ev0, s));
+  if (table) {
+    HIP_TRY(ctx, launch_out_table(L, table, s));
+    L.tab = table;
+  }
   HIP_TRY(ctx, launch_outputs(L, s));
   HIP_TRY(ctx, hipEventRecord(ctx->ev1, s));
   ctx->timed = true;

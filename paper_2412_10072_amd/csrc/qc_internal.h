@@ -540,8 +540,14 @@ struct OutputLaunch {
   int w_vec;                  // corrected weights: 4 per sample, weights and out 16-byte aligned
   void* out;
   SkyArgs sky;                // sky.comp non-null: the model is predicted from it per sample
+  // the direction-independent chain, [n_time][n_ant][n_chan] pairs of the
+  // diagonal's entries (diag_chain) or 2x2 products, of the data precision; null:
+  // formed per sample
+  const void* tab;
 };
 
+size_t out_table_bytes(const OutputLaunch& L);
+hipError_t launch_out_table(const OutputLaunch& L, void* table, hipStream_t stream);
 hipError_t launch_outputs(const OutputLaunch& L, hipStream_t stream);
 
 }  // namespace qc

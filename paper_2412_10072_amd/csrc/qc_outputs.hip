@@ -11,12 +11,27 @@
 //             chains); one weight per sample takes the mean of the four factors.
 //
 // Each wavefront takes one row at a time (antennas and time are uniform) and
-// its lanes consecutive channels, so every load and store is contiguous.  Arithmetic is in the data precision.
+// its lanes consecutive channels, so every load and store is contiguous; where
+// that would leave many lanes without a channel, it takes 64 samples as they lie
+// in memory, over several rows.  Bound by streaming (5.5 TB/s for one term whose
+// gains a wavefront shares).  A chain that takes more than one shared gain block
+// per row -- several terms, phasors, solutions narrower than a wavefront's
+// channels -- is evaluated once per (time, antenna, channel) into a table
+// (k_out_table) instead of once per sample and antenna, 31 times as often for 64
+// antennas; a sample reads 16 bytes per antenna of it (32 for full products).
+// Arithmetic is in the data precision, the same products in either case.
+
+#include <algorithm>
 
 #include "qc_internal.h"
 
 namespace qc {
 namespace {
+
+// The row form where its lanes are at most this many times the channels: 16
+// channels (40 antennas, 100 times) take 67 us by rows and 31 flat, 83 channels
+// (1.54 times as many lanes) 418 and 399.
+constexpr double FLAT_LANES = 1.3;
 
 template <typename S, typename T>
 __device__ __forceinline__ m22<T> ld(const S* base, size_t elem) {
@@ -108,7 +123,9 @@ __device__ __forceinline__ void corrected_weight(const VisArgs& V, size_t s, cx<
 // of complex numbers and the direction-independent part is formed once per
 // sample.  SKY (CORRUPT and RESIDUAL): the model is predicted per sample from
 // L.sky's point components instead of read.
-template <typename S, int MODE, bool DIAG, bool SKY = false>
+// FLAT: 64 consecutive samples per wavefront step, over rows.  TAB: the
+// direction-independent chain is read from L.tab.
+template <typename S, int MODE, bool DIAG, bool SKY, bool FLAT, bool TAB>
 __global__ void __launch_bounds__(256) k_outputs(OutputLaunch L) {
   using T = S;
   const VisArgs& V = L.vis;
@@ -119,12 +136,10 @@ __global__ void __launch_bounds__(256) k_outputs(OutputLaunch L) {
   const int nw = blockDim.x >> 6;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lane = threadIdx.x & 63;
-  for (long long r = (long long)blockIdx.x * nw + wave; r < V.n_row; r += (long long)gridDim.x * nw)
-  for (int c = lane; c < V.n_chan; c += 64) {
-    // one row per wavefront (antennas and time uniform), lanes over channels
-    const size_t s = (size_t)r * V.n_chan + c;
+  const cx<T>* tab = reinterpret_cast<const cx<T>*>(L.tab);
+  auto sample = [&](size_t s, long long r, int c) {
     const int p = V.ant1[r], q = V.ant2[r], t = V.row_time[r];
-    if ((unsigned)p >= (unsigned)V.n_ant || (unsigned)q >= (unsigned)V.n_ant) continue;
+    if ((unsigned)p >= (unsigned)V.n_ant || (unsigned)q >= (unsigned)V.n_ant) return;
     const double nu = V.freq[c];
     // the model of direction d: read, or predicted with the baseline in wavelengths
     double un = 0.0, vn = 0.0, wn = 0.0, lnu = 0.0;
@@ -138,10 +153,26 @@ __global__ void __launch_bounds__(256) k_outputs(OutputLaunch L) {
       if constexpr (SKY) return sky_model<T>(L.sky, un, vn, wn, lnu, d);
       else return ld<S, T>(Mp, s * V.n_dir + d);
     };
+    // the whole chain of antenna x (with a table: direction independent)
+    auto whole = [&](int x, int d) -> m22<T> {
+      if constexpr (TAB) {
+        const cx<T>* e = tab + (((size_t)t * V.n_ant + x) * V.n_chan + c) * 4;
+        return {e[0], e[1], e[2], e[3]};
+      } else {
+        return chain_range<T>(CH, V.n_ant, 0, CH.n_term, t, c, x, d, nu);
+      }
+    };
     if constexpr (DIAG) {
       cx<T> p0 = cone<T>(), p1 = cone<T>(), q0 = cone<T>(), q1 = cone<T>();
-      diag_part<T, false>(CH, V.n_ant, t, c, p, 0, nu, p0, p1);
-      diag_part<T, false>(CH, V.n_ant, t, c, q, 0, nu, q0, q1);
+      if constexpr (TAB) {
+        const cx<T>* tp = tab + (((size_t)t * V.n_ant + p) * V.n_chan + c) * 2;
+        const cx<T>* tq = tab + (((size_t)t * V.n_ant + q) * V.n_chan + c) * 2;
+        p0 = tp[0]; p1 = tp[1];
+        q0 = tq[0]; q1 = tq[1];
+      } else {
+        diag_part<T, false>(CH, V.n_ant, t, c, p, 0, nu, p0, p1);
+        diag_part<T, false>(CH, V.n_ant, t, c, q, 0, nu, q0, q1);
+      }
       if constexpr (MODE == 1 || MODE == 3) {
         // a direction-independent chain: terms with several gain directions
         // map every direction to one, so direction 0 stands for all
@@ -191,12 +222,12 @@ __global__ void __launch_bounds__(256) k_outputs(OutputLaunch L) {
         st<S, T>(Op, s, Vm);
       }
     } else if constexpr (MODE == 3) {
-      const m22<T> Cp = chain_range<T>(CH, V.n_ant, 0, CH.n_term, t, c, p, 0, nu);
-      const m22<T> Cq = chain_range<T>(CH, V.n_ant, 0, CH.n_term, t, c, q, 0, nu);
+      const m22<T> Cp = whole(p, 0);
+      const m22<T> Cq = whole(q, 0);
       corrected_weight<S, T>(V, s, Cp.a, Cp.d, Cq.a, Cq.d, Op, L.w_vec != 0);
     } else if constexpr (MODE == 1) {
-      const m22<T> Cp = chain_range<T>(CH, V.n_ant, 0, CH.n_term, t, c, p, 0, nu);
-      const m22<T> Cq = chain_range<T>(CH, V.n_ant, 0, CH.n_term, t, c, q, 0, nu);
+      const m22<T> Cp = whole(p, 0);
+      const m22<T> Cq = whole(q, 0);
       m22<T> ip, iq;
       const bool okp = inv2(Cp, ip), okq = inv2(Cq, iq);
       m22<T> o = mzero<T>();
@@ -206,53 +237,119 @@ __global__ void __launch_bounds__(256) k_outputs(OutputLaunch L) {
       m22<T> Vm = mzero<T>();
       for (int d = 0; d < V.n_dir; ++d) {
         if (!((L.dir_mask >> d) & 1u)) continue;
-        const m22<T> Cp = chain_range<T>(CH, V.n_ant, 0, CH.n_term, t, c, p, d, nu);
-        const m22<T> Cq = chain_range<T>(CH, V.n_ant, 0, CH.n_term, t, c, q, d, nu);
+        const m22<T> Cp = whole(p, d);
+        const m22<T> Cq = whole(q, d);
         Vm = Vm + mmul_h(mmul(Cp, model_at(d)), Cq);
       }
       if constexpr (MODE == 2) Vm = ld<S, T>(Dp, s) - Vm;
       st<S, T>(Op, s, Vm);
     }
+  };
+  const long long first = (long long)blockIdx.x * nw + wave, step = (long long)gridDim.x * nw;
+  if constexpr (FLAT) {
+    const long long n = V.n_row * V.n_chan;
+    for (long long s0 = first * 64; s0 < n; s0 += step * 64) {
+      const long long rb = s0 / V.n_chan;            // uniform
+      const unsigned off = (unsigned)(s0 - rb * V.n_chan) + lane;
+      const unsigned dr = off / (unsigned)V.n_chan;
+      if (s0 + lane < n) sample((size_t)(s0 + lane), rb + dr, (int)(off - dr * (unsigned)V.n_chan));
+    }
+  } else {
+    for (long long r = first; r < V.n_row; r += step)
+      for (int c = lane; c < V.n_chan; c += 64) sample((size_t)r * V.n_chan + c, r, c);
   }
+}
+
+// The direction-independent chain at every (time, antenna, channel): diagonals
+// of the terms with one gain direction (DIAG), or the whole 2x2 product.
+template <typename T, bool DIAG>
+__global__ void __launch_bounds__(256) k_out_table(OutputLaunch L, cx<T>* out) {
+  const VisArgs& V = L.vis;
+  const long long n = (long long)V.n_time * V.n_ant * V.n_chan;
+  const long long i = (long long)blockIdx.x * 256 + threadIdx.x;
+  if (i >= n) return;
+  const int c = (int)(i % V.n_chan);
+  const int ta = (int)(i / V.n_chan);
+  const int t = ta / V.n_ant, a = ta - t * V.n_ant;
+  const double nu = V.freq[c];
+  if constexpr (DIAG) {
+    cx<T> h0 = cone<T>(), h1 = cone<T>();
+    diag_part<T, false>(L.chain, V.n_ant, t, c, a, 0, nu, h0, h1);
+    out[2 * i] = h0;
+    out[2 * i + 1] = h1;
+  } else {
+    const m22<T> C = chain_range<T>(L.chain, V.n_ant, 0, L.chain.n_term, t, c, a, 0, nu);
+    out[4 * i] = C.a;
+    out[4 * i + 1] = C.b;
+    out[4 * i + 2] = C.c;
+    out[4 * i + 3] = C.d;
+  }
+}
+
+template <typename S, int MODE, bool DIAG, bool SKY>
+hipError_t launch_mode(const OutputLaunch& L, hipStream_t stream) {
+  const long long n_row = L.vis.n_row, n_chan = L.vis.n_chan;
+  const bool flat = (double)((n_chan + 63) / 64 * 64) > FLAT_LANES * (double)n_chan;
+  const long long steps = flat ? (n_row * n_chan + 63) / 64 : n_row;     // of a wavefront
+  const dim3 g((unsigned)std::min<long long>((steps + 3) / 4, 256 * 64)), b(256);
+  if constexpr (!SKY) {
+    if (L.tab) {
+      if (flat) hipLaunchKernelGGL((k_outputs<S, MODE, DIAG, false, true, true>), g, b, 0, stream, L);
+      else hipLaunchKernelGGL((k_outputs<S, MODE, DIAG, false, false, true>), g, b, 0, stream, L);
+      return hipGetLastError();
+    }
+  }
+  if (flat) hipLaunchKernelGGL((k_outputs<S, MODE, DIAG, SKY, true, false>), g, b, 0, stream, L);
+  else hipLaunchKernelGGL((k_outputs<S, MODE, DIAG, SKY, false, false>), g, b, 0, stream, L);
+  return hipGetLastError();
 }
 
 template <typename S>
 hipError_t launch_s(const OutputLaunch& L, hipStream_t stream) {
-  const size_t n = (size_t)L.vis.n_row * L.vis.n_chan;
-  if (n == 0) return hipSuccess;
-  size_t blocks = ((size_t)L.vis.n_row + 3) / 4;     // 4 wavefronts of one row each
-  if (blocks > 256 * 64) blocks = 256 * 64;
-  const dim3 g((unsigned)blocks), b(256);
+  if (L.vis.n_row == 0 || L.vis.n_chan == 0) return hipSuccess;
   if (L.sky.comp) {
     if (L.mode != 0 && L.mode != 2) return hipErrorNotSupported;
-    if (L.diag_chain) {
-      if (L.mode == 0) hipLaunchKernelGGL((k_outputs<S, 0, true, true>), g, b, 0, stream, L);
-      else hipLaunchKernelGGL((k_outputs<S, 2, true, true>), g, b, 0, stream, L);
-    } else {
-      if (L.mode == 0) hipLaunchKernelGGL((k_outputs<S, 0, false, true>), g, b, 0, stream, L);
-      else hipLaunchKernelGGL((k_outputs<S, 2, false, true>), g, b, 0, stream, L);
-    }
-    return hipGetLastError();
+    if (L.diag_chain) return L.mode == 0 ? launch_mode<S, 0, true, true>(L, stream) : launch_mode<S, 2, true, true>(L, stream);
+    return L.mode == 0 ? launch_mode<S, 0, false, true>(L, stream) : launch_mode<S, 2, false, true>(L, stream);
   }
   if (L.diag_chain) {
     switch (L.mode) {
-      case 0: hipLaunchKernelGGL((k_outputs<S, 0, true>), g, b, 0, stream, L); break;
-      case 1: hipLaunchKernelGGL((k_outputs<S, 1, true>), g, b, 0, stream, L); break;
-      case 3: hipLaunchKernelGGL((k_outputs<S, 3, true>), g, b, 0, stream, L); break;
-      default: hipLaunchKernelGGL((k_outputs<S, 2, true>), g, b, 0, stream, L); break;
-    }
-  } else {
-    switch (L.mode) {
-      case 0: hipLaunchKernelGGL((k_outputs<S, 0, false>), g, b, 0, stream, L); break;
-      case 1: hipLaunchKernelGGL((k_outputs<S, 1, false>), g, b, 0, stream, L); break;
-      case 3: hipLaunchKernelGGL((k_outputs<S, 3, false>), g, b, 0, stream, L); break;
-      default: hipLaunchKernelGGL((k_outputs<S, 2, false>), g, b, 0, stream, L); break;
+      case 0: return launch_mode<S, 0, true, false>(L, stream);
+      case 1: return launch_mode<S, 1, true, false>(L, stream);
+      case 3: return launch_mode<S, 3, true, false>(L, stream);
+      default: return launch_mode<S, 2, true, false>(L, stream);
     }
   }
+  switch (L.mode) {
+    case 0: return launch_mode<S, 0, false, false>(L, stream);
+    case 1: return launch_mode<S, 1, false, false>(L, stream);
+    case 3: return launch_mode<S, 3, false, false>(L, stream);
+    default: return launch_mode<S, 2, false, false>(L, stream);
+  }
+}
+
+template <typename T>
+hipError_t launch_table(const OutputLaunch& L, void* table, hipStream_t stream) {
+  const long long n = (long long)L.vis.n_time * L.vis.n_ant * L.vis.n_chan;
+  if (n == 0) return hipSuccess;
+  const long long grid = (n + 255) / 256;
+  if (grid > 0x7fffffffLL) return hipErrorInvalidValue;
+  cx<T>* out = reinterpret_cast<cx<T>*>(table);
+  if (L.diag_chain) hipLaunchKernelGGL((k_out_table<T, true>), dim3((unsigned)grid), dim3(256), 0, stream, L, out);
+  else hipLaunchKernelGGL((k_out_table<T, false>), dim3((unsigned)grid), dim3(256), 0, stream, L, out);
   return hipGetLastError();
 }
 
 }  // namespace
+
+size_t out_table_bytes(const OutputLaunch& L) {
+  return (size_t)L.vis.n_time * L.vis.n_ant * L.vis.n_chan * (L.diag_chain ? 2 : 4) *
+         (L.vis_is_c128 ? sizeof(cx<double>) : sizeof(cx<float>));
+}
+
+hipError_t launch_out_table(const OutputLaunch& L, void* table, hipStream_t stream) {
+  return L.vis_is_c128 ? launch_table<double>(L, table, stream) : launch_table<float>(L, table, stream);
+}
 
 hipError_t launch_outputs(const OutputLaunch& L, hipStream_t stream) {
   return L.vis_is_c128 ? launch_s<double>(L, stream) : launch_s<float>(L, stream);
