@@ -251,6 +251,11 @@ typedef struct {
  * for COMPLEX2X2, 2x2 for DIAGONAL, real 2x2 for DELAY / PHASE / AMPLITUDE,
  * real 4x4 for DELAY_OFFSET, whose pivots are then each tested against their
  * own diagonal entry), one row per wavefront step.
+ * The context keeps scratch memory between calls.  Its largest part is the
+ * folded model of a diagonal chain (one direction of the model's size, where
+ * the active term has one gain direction): at most a sixteenth of the device's
+ * memory and an eighth of what was free when it was allocated; without room the
+ * solve reads the model itself.  qc_ctx_destroy gives it back.
  */
 qc_status qc_solve_interval(qc_ctx* ctx, const qc_vis* vis, qc_term* chain, int32_t n_term,
                             int32_t active, const qc_solve_opts* opts, qc_solve_stats* stats);

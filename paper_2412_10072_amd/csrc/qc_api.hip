@@ -340,6 +340,7 @@ qc_status qc_ctx_destroy(qc_ctx* ctx) {
   hipFree(ctx->d_dh);
   hipFree(ctx->d_partials);
   hipFree(ctx->d_otab);
+  hipFree(ctx->d_fold);
   hipFree(ctx->d_fl_stat);
   hipFree(ctx->d_fl_groups);
   hipFree(ctx->d_fl_hist);
@@ -409,22 +410,22 @@ double qc_last_kernel_ms(qc_ctx* ctx) {
 // 12 us beyond its steps fused and 25 us split.  Levenberg-Marquardt keeps to large
 // intervals (2^18 samples on average): its accepted steps hang on the last bits
 // of chi^2, which differ between the schedules.
-static int split_parts(const qc_ctx* ctx, const qc_vis* vis, const qc_term& ta, int n_term, const SolveLaunch& L,
+static int split_parts(const qc_ctx* ctx, const qc_vis* vis, const qc_term& ta, bool single, const SolveLaunch& L,
                        bool lm) {
   const int n_int = ta.n_gt * ta.n_gf;
   const double n_samples = (double)vis->n_row * vis->n_chan;
   const double rows = (double)vis->n_row / std::max(ta.n_gt, 1);
   const double avg = n_samples / n_int;
-  const bool single = n_term == 1 && vis->n_dir == 1 && ta.n_gdir == 1;
+  const int n_dir = single ? 1 : vis->n_dir;
   const bool fp64 = !L.prec_mixed;
   const bool lane_rows = !single && L.max_int_chan <= 4 && ta.n_gdir == 1 && !L.left_general;
   const int rps = single ? 4 : lane_rows ? 64 : 1;
   const double chunks = lane_rows ? L.max_int_chan : std::ceil(L.max_int_chan / (64.0 / rps));
   const double steps = std::ceil(rows / (4.0 * rps)) * chunks;
-  const double step_us = single ? 1.25 : lane_rows ? 10.0 : 1.25 * (1.0 + 0.75 * vis->n_dir);
+  const double step_us = single ? 1.25 : lane_rows ? 10.0 : 1.25 * (1.0 + 0.75 * n_dir);
   const int fit = ctx->n_cu * (fp64 ? 2 : single ? 4 : 3);
   const double real = L.vis_is_c128 ? 8.0 : 4.0;
-  const double pass_bytes = n_samples * (real * (8.0 + 8.0 * vis->n_dir + vis->n_wcorr) + 1.0);
+  const double pass_bytes = n_samples * (real * (8.0 + 8.0 * n_dir + vis->n_wcorr) + 1.0);
   const double stream_us = pass_bytes / 6e6;                     // 6 TB/s
   const bool large = n_int < 4 * ctx->n_cu && avg >= (double)(1 << 18);   // split whatever the estimate
   if (lm && !large) return 1;
@@ -442,6 +443,23 @@ static int split_parts(const qc_ctx* ctx, const qc_vis* vis, const qc_term& ta, 
   // the partial sums (24 values per block at most) stay below 2 GiB
   const double blocks = (double)n_int * parts * vis->n_ant * (ta.n_gdir == 1 ? 1 : 4);
   return blocks * 24.0 * sizeof(double) > 2147483648.0 ? 1 : parts;
+}
+
+// Memory for a folded model in the context: at most a sixteenth of the device's,
+// and, when it has to grow, an eighth of what is free (the arrays the caller
+// may still want come first); false: the solve goes without.
+static bool fold_memory(qc_ctx* ctx, size_t bytes) {
+  if (bytes == 0) return false;
+  if (ctx->d_fold && bytes <= ctx->fold_cap) return true;
+  size_t free_b = 0, total_b = 0;
+  if (hipMemGetInfo(&free_b, &total_b) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  if (bytes > total_b / 16 || bytes > free_b / 8) return false;
+  if (grow(ctx->d_fold, ctx->fold_cap, bytes) == hipSuccess) return true;
+  (void)hipGetLastError();
+  return false;
 }
 
 // qc_solve_interval; fixed != NULL: the allocation-free form (prepare scratch
@@ -538,6 +556,19 @@ static qc_status solve_interval_impl(qc_ctx* ctx, const qc_vis* vis, qc_term* ch
   const int n_int = ta.n_gt * ta.n_gf;
   int parts = 1;
   const bool lm = opts->damping == QC_DAMP_LM;
+  const bool single_chain = (n_term == 1 && vis->n_dir == 1 && ta.n_gdir == 1);
+  // intervals of one channel each, in channel order, for the band pass below
+  bool one_chan = ta.type == QC_TERM_DIAGONAL && ctx->max_int_chan == 1 && ta.n_gf == vis->n_chan;
+  for (int g = 0; one_chan && g < ta.n_gf; ++g)
+    if (ctx->h_clo[g] != g) one_chan = false;
+  // A diagonal chain whose active term has one gain direction: folded into one
+  // model where several passes will read it, the model is stored as it is
+  // computed (MIXED of complex64, FP64 of complex128) and the memory is there.
+  // (Levenberg-Marquardt keeps its arithmetic; intervals of 2 to 4 channels keep
+  // the one-row-per-lane kernel of chains.)
+  bool fold = !fixed && !sky && !lm && L.diag_chain && !single_chain && ta.n_gdir == 1 && opts->max_iter >= 3 &&
+              L.prec_mixed != L.vis_is_c128 && (one_chan || ctx->max_int_chan > 4);
+  if (fold) fold = fold_memory(ctx, chain_fold_bytes(L));
   if (lm && ta.type == QC_TERM_DELAY_OFFSET)
     return fail(ctx, QC_E_UNSUPPORTED, "Levenberg-Marquardt takes no delay-and-offset term");
   if (fixed) {
@@ -545,17 +576,14 @@ static qc_status solve_interval_impl(qc_ctx* ctx, const qc_vis* vis, qc_term* ch
   } else if (ctx->split_parts > 1) {
     parts = ctx->split_parts;
   } else if (ctx->split_parts == 0 && !opts->chisq_ref && n_int > 0) {
-    parts = split_parts(ctx, vis, ta, n_term, L, lm);
+    parts = split_parts(ctx, vis, ta, single_chain || fold, L, lm);
   }
   if (parts > 1 && opts->chisq_ref)
     return fail(ctx, QC_E_UNSUPPORTED, "the split schedule does not take chisq_ref");
   // intervals of one channel each, in channel order, on a diagonal chain with
   // one gain direction: the split pass over 16 channels per wavefront
-  bool band = parts > 1 && !sky && L.diag_chain && !L.left_general && ta.type == QC_TERM_DIAGONAL &&
-              ta.n_gdir == 1 && ctx->max_int_chan == 1 && ta.n_gf == vis->n_chan && vis->n_row < (1LL << 31) &&
-              band_lds_bytes_for(vis->n_ant, L.prec_mixed != 0, 8) <= 64 * 1024;
-  for (int g = 0; band && g < ta.n_gf; ++g)
-    if (ctx->h_clo[g] != g) band = false;
+  bool band = parts > 1 && !sky && L.diag_chain && !L.left_general && one_chan && ta.n_gdir == 1 &&
+              vis->n_row < (1LL << 31) && band_lds_bytes_for(vis->n_ant, L.prec_mixed != 0, 8) <= 64 * 1024;
   // diagonal chains: the direction-dependent fixed terms, when all are
   // diagonal gains and at most BAND_MAX_DD, tabulated once per solve for every
   // pass (the band pass takes no other kind).  A pointing term differs by
@@ -569,7 +597,7 @@ static qc_status solve_interval_impl(qc_ctx* ctx, const qc_vis* vis, qc_term* ch
     else L.dd_term[L.n_dd++] = j;
   }
   if (!L.dd_tabled) L.n_dd = 0;
-  if (!L.dd_tabled) band = false;
+  if (!L.dd_tabled && !fold) band = false;
   // 4 rows x 16 channels per step (measured faster than 8 x 8 on the 64-antenna
   // bandpass: 11.1 against 12.9 ms per pass), unless asked otherwise or its LDS
   // slots do not fit
@@ -583,7 +611,6 @@ static qc_status solve_interval_impl(qc_ctx* ctx, const qc_vis* vis, qc_term* ch
   ctx->last_split_parts = parts;
   // diagonal chains: the direction-independent terms other than the active
   // one are fixed during the solve; tabulate their product once
-  const bool single_chain = (n_term == 1 && vis->n_dir == 1 && ta.n_gdir == 1);
   bool other_di = false;
   for (int j = 0; j < n_term; ++j)
     if (j != active && chain[j].n_gdir == 1) other_di = true;
@@ -656,6 +683,19 @@ static qc_status solve_interval_impl(qc_ctx* ctx, const qc_vis* vis, qc_term* ch
   for (int j = 0; j < L.n_dd && e == hipSuccess; ++j) {
     L.dd_tab[j] = ctx->d_ddtab + dd_off[j];
     e = launch_dd_table(L, L.dd_term[j], ctx->d_ddtab + dd_off[j], s);
+  }
+  if (fold && e == hipSuccess) {
+    e = launch_chain_fold(L, ctx->d_fold, s);
+    // from here the solve is that of the active term alone over the folded model
+    L.vis.model = ctx->d_fold;
+    L.vis.n_dir = 1;
+    L.chain.t[0] = L.chain.t[active];
+    L.chain.active = 0;
+    L.chain.n_term = 1;
+    L.otab = nullptr;
+    L.n_dd = 0;
+    L.dd_tabled = 1;
+    L.dir_ident = 0;
   }
   if (e != hipSuccess) {
     // reported below

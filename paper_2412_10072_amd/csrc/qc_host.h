@@ -63,6 +63,8 @@ struct qc_ctx {
   size_t partials_cap = 0;
   unsigned char* d_otab = nullptr;    // fixed chain factors of diagonal chains
   size_t otab_cap = 0;
+  unsigned char* d_fold = nullptr;    // folded model of a diagonal chain's solve
+  size_t fold_cap = 0;
   // MAD flagging scratch
   unsigned char* d_fl_stat = nullptr;  // per-sample statistic
   size_t fl_stat_cap = 0;

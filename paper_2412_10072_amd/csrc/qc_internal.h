@@ -434,6 +434,11 @@ hipError_t launch_dd_table(const SolveLaunch& L, int j, void* table, hipStream_t
 size_t chain_table_bytes(const SolveLaunch& L);
 hipError_t launch_chain_table(const SolveLaunch& L, void* table, hipStream_t stream);
 
+// The chain of a solve folded into one model (k_chain_fold): `bytes` of memory,
+// and the fill on `stream` (after L.otab and the L.dd_tab tables).
+size_t chain_fold_bytes(const SolveLaunch& L);
+hipError_t launch_chain_fold(const SolveLaunch& L, void* out, hipStream_t stream);
+
 // Split schedule (see qc_solve.hip): per-interval iteration state in device
 // memory; phase 0 resets it, phase 1 runs one pass + update over every
 // active interval.
