@@ -361,6 +361,7 @@ qc_status qc_ctx_destroy(qc_ctx* ctx) {
   hipFree(ctx->d_lm);
   hipFree(ctx->d_acc);
   hipFree(ctx->d_band);
+  hipFree(ctx->d_bandg);
   hipFree(ctx->d_ddtab);
   hipEventDestroy(ctx->ev0);
   hipEventDestroy(ctx->ev1);
@@ -605,7 +606,8 @@ static qc_status solve_interval_impl(qc_ctx* ctx, const qc_vis* vis, qc_term* ch
   if (band && ctx->split_parts == 0) {
     const long long units = (long long)((vis->n_chan + 64 / L.band_rows - 1) / (64 / L.band_rows)) * ta.n_gt;
     const double rows_per_int = (double)vis->n_row / std::max(ta.n_gt, 1);
-    parts = (int)std::ceil((double)BAND_WAVES_PER_CU * ctx->n_cu / (double)units);
+    const int fit = (int)(160 * 1024 / band_lds_bytes_for(vis->n_ant, L.prec_mixed != 0, L.band_rows));
+    parts = (int)((long long)std::max(1, std::min(BAND_WAVES_PER_CU, fit)) * ctx->n_cu / units);
     parts = std::max(2, std::min(parts, (int)std::max(1.0, rows_per_int / 32.0)));
   }
   ctx->last_split_parts = parts;
@@ -660,7 +662,13 @@ static qc_status solve_interval_impl(qc_ctx* ctx, const qc_vis* vis, qc_term* ch
     }
   }
   size_t dd_off[BAND_MAX_DD] = {0, 0};
-  if (band) HIP_TRY(ctx, grow(ctx->d_band, ctx->band_cap, (size_t)std::max<long long>(vis->n_row, 1)));
+  L.band_gains = nullptr;
+  if (band && (fold || single_chain)) {
+    HIP_TRY(ctx, grow(ctx->d_bandg, ctx->bandg_cap, band_gains_bytes(L)));
+    L.band_gains = ctx->d_bandg;
+  } else if (band) {
+    HIP_TRY(ctx, grow(ctx->d_band, ctx->band_cap, (size_t)std::max<long long>(vis->n_row, 1)));
+  }
   if (L.n_dd > 0) {
     size_t dd_bytes = 0;
     for (int j = 0; j < L.n_dd; ++j) {
@@ -676,7 +684,7 @@ static qc_status solve_interval_impl(qc_ctx* ctx, const qc_vis* vis, qc_term* ch
     e = launch_chain_table(L, ctx->d_otab, s);
     L.otab = ctx->d_otab;
   }
-  if (band && e == hipSuccess) {
+  if (band && !L.band_gains && e == hipSuccess) {
     e = launch_band_steps(L, parts, L.band_rows, ctx->d_band, s);
     L.band_steps = ctx->d_band;
   }

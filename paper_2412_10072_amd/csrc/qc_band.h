@@ -17,9 +17,9 @@
 // antenna p and differ in antenna q (a p-run of the row order).  The
 // antenna-p sums stay in registers over the run and are summed over the rows
 // of the step when p changes; the antenna-q sums go straight to the wavefront's LDS slots
-// [antenna][value][channel], which the lanes of one step address without
-// collision (distinct q per row, distinct channel per lane), so LDS atomics
-// add them in program order and the result does not depend on timing.  At
+// [antenna][channel][value], which the lanes of one step address without
+// collision (distinct q per row, distinct channel per lane), so they are added in
+// program order and the result does not depend on timing.  At
 // each change of time the LDS slots are added into the part's FP64 partial
 // blocks (in the layout the split update sums), so an FP32 slot holds at most
 // one time's sums (<= n_ant - 1 rows per antenna).
@@ -48,10 +48,50 @@ __device__ __forceinline__ BandStep band_step_at(const BandStep* steps, long lon
   return s;
 }
 
-// LDS slot of (antenna, value, channel) for CW channels per wavefront
+// LDS slot of (antenna, value, channel) for CW channels per wavefront: the
+// values of one (antenna, channel) side by side, so that a lane adds its six with
+// three 8-byte (FP64: 16-byte) reads and writes.
 template <typename A, int CW>
 __device__ __forceinline__ A* band_slot(int ant, int k, int cl) {
-  return lds_at<A>(0) + ((size_t)ant * BAND_NV + k) * CW + cl;
+  return lds_at<A>(0) + ((size_t)ant * CW + cl) * BAND_NV + k;
+}
+
+// Adds a lane's values to the slots of (ant, channel cl).  The lanes of one call
+// address distinct slots and only this wavefront does, so plain reads and writes
+// do: as LDS atomics (six per step, rows colliding on banks) the additions were
+// what bounded the pass, at 2.2 TB/s whatever was loaded ahead (1.24 ms for 256
+// channels x 60 times of 64 antennas, with these 0.68, and 0.55 in one round of
+// workgroups).
+template <typename A, int CW>
+__device__ __forceinline__ void band_add(int ant, int cl, const A* v) {
+  using A2 = A __attribute__((ext_vector_type(2)));
+  A2* s = reinterpret_cast<A2*>(band_slot<A, CW>(ant, 0, cl));
+  static_assert(BAND_NV == 6, "three pairs");
+  A2 x[3];
+#pragma unroll
+  for (int j = 0; j < 3; ++j) x[j] = s[j];
+#pragma unroll
+  for (int j = 0; j < 3; ++j) s[j] = x[j] + A2{v[2 * j], v[2 * j + 1]};
+}
+
+// Keeps a lane's additions before it apart from those after it, which other
+// lanes may have made to the same slots meanwhile (no instruction: a wavefront's
+// LDS operations are performed in order).
+__device__ __forceinline__ void band_turn() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
+// The same, the rows of a step one after the other (their slots may be the same):
+// lane (g, cl) adds where `add` is set.  (To one lane, which has its own turn only,
+// the turns would be one addition.)
+template <typename A, int CW>
+__device__ __forceinline__ void band_add_turns(bool add, int g, int ant, int cl, const A* v) {
+#pragma unroll
+  for (int h = 0; h < 64 / CW; ++h) {
+    if (add && g == h) band_add<A, CW>(ant, cl, v);
+    band_turn();
+  }
 }
 
 // x of the lane 8 apart in the same 16-lane row (DPP row rotate by 8)
@@ -174,18 +214,19 @@ __global__ void __launch_bounds__(64) k_band_pass(SolveLaunch L, int n_part, dou
       const int k = PER * g + j;
       if (k < NV && cin) lds_add(band_slot<A, CW>(p_cur, k, cl), pacc[j]);
     }
+    band_turn();
 #pragma unroll
     for (int k = 0; k < 8; ++k) pacc[k] = A(0);
   };
   // the LDS slots added into the part's FP64 blocks, and cleared
   auto flush_lds = [&]() {
     __syncthreads();
-    for (int i = lane; i < n_vals; i += 64) {
-      A* ps = lds_at<A>(0) + i;
+    for (int i = g; i < n_ant * NV; i += NR) {     // (antenna, value)
+      A* ps = band_slot<A, CW>(i / NV, i % NV, cl);
       const double x = (double)*ps;
       *ps = A(0);
       if (cin) {
-        double* dst = Pc + i / CW;          // (antenna, value); i % CW == cl
+        double* dst = Pc + i;
         *dst = first ? x : *dst + x;
       }
     }
@@ -314,18 +355,11 @@ __global__ void __launch_bounds__(64) k_band_pass(SolveLaunch L, int n_part, dou
 
     const bool add = row_ok && cin;
     if (!st.dup) {
-      if (add) {
-#pragma unroll
-        for (int k = 0; k < NV; ++k) lds_add(band_slot<A, CW>(q, k, cl), qv[k]);
-      }
+      if (add) band_add<A, CW>(q, cl, qv);
+      band_turn();
     } else {
       // two rows of the step share antenna q: one row at a time
-      for (int h = 0; h < NR; ++h) {
-        if (add && g == h) {
-#pragma unroll
-          for (int k = 0; k < NV; ++k) lds_add(band_slot<A, CW>(q, k, cl), qv[k]);
-        }
-      }
+      band_add_turns<A, CW>(add, g, q, cl, qv);
     }
     r = r_next;
     st = nx;
@@ -338,6 +372,246 @@ __global__ void __launch_bounds__(64) k_band_pass(SolveLaunch L, int n_part, dou
   cs = band_full<16>(cs);
   if constexpr (CW == 8) cs = band_full<8>(cs);
   if (g == 0 && cin) Pc[stride - 1] = cs;
+}
+
+// ---------------------------------------------------------------------------
+// The same pass where the model is one direction and the chain the active term
+// alone (as it is over a folded chain): no fixed factors.
+//
+// Bound by latency: six wavefronts per CU (24 KiB of LDS each at 64 antennas)
+// and 64 samples a step.  So a step is simply the next four (eight) rows, whose
+// samples are loaded two steps ahead and whose antennas and gains one step ahead
+// (the steps above wait for one another's records), and the gains come from a
+// table in the step's own layout [gain time][slice][antenna][hand][channel]
+// (k_band_gains, once per pass: 8 cache lines a step instead of one per lane out
+// of the solution's FP64 blocks, which lie an interval apart).  The rows of a step
+// may differ in antenna p: each lane keeps its own row's p sums and adds them to
+// LDS, one row after the other, when its p changes.  Folded bandpass of 256
+// channels, 64 antennas, 60 times (2.5 GB a pass): 1.24 -> 0.55 ms.
+// ---------------------------------------------------------------------------
+template <typename T, int CW>
+__global__ void __launch_bounds__(256) k_band_gains(const double2* gains, int n_gf, int n_ant, int n_slices, size_t n,
+                                                    cx<T>* tab) {
+  const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
+  if (i >= n) return;
+  const int cl = (int)(i % CW);
+  size_t j = i / CW;
+  const int hand = (int)(j & 1);
+  j >>= 1;
+  const int a = (int)(j % n_ant);
+  j /= n_ant;
+  const int slice = (int)(j % n_slices);
+  const size_t gt = j / n_slices;
+  const int c = min(slice * CW + cl, n_gf - 1);        // lanes past the band repeat the last channel
+  const double2 g = gains[4 * ((gt * n_gf + c) * n_ant + a) + 3 * hand];
+  tab[i] = cmake<T>((T)g.x, (T)g.y);
+}
+
+template <typename T>
+struct BandRow {
+  int p, q, t;               // of this lane's row; q = -1: the row adds nothing
+};
+template <typename T>
+struct BandGain {
+  cx<T> p0, p1, q0, q1;
+};
+
+template <typename S, typename T, int CW>
+__global__ void __launch_bounds__(64) k_band_single(SolveLaunch L, int n_part, double* partials, const uint8_t* done) {
+  using A = T;
+  constexpr int NV = BAND_NV;
+  constexpr int NR = 64 / CW;           // rows per step
+  const VisArgs& V = L.vis;
+  const TermArgs& TA = L.chain.t[L.chain.active];
+  const int n_ant = V.n_ant;
+  const int n_chan = V.n_chan;
+  const int n_gf = TA.n_gf;
+  const int n_slices = (n_chan + CW - 1) / CW;
+  const int slice = blockIdx.x % n_slices;
+  const int rest = blockIdx.x / n_slices;
+  const int part = rest % n_part;
+  const int gt = rest / n_part;
+  const int lane = threadIdx.x;
+  const int cl = lane & (CW - 1);
+  const int g = lane / CW;
+  const int c = slice * CW + cl;
+  const bool cin = c < n_chan;
+  const int cc = cin ? c : n_chan - 1;
+  const int interval = gt * n_gf + cc;       // one channel per interval: gain frequency = channel
+  if (!__any(cin && !done[interval])) return;
+
+  const int n_vals = n_ant * NV * CW;
+  for (int i = lane; i < n_vals; i += 64) lds_at<A>(0)[i] = A(0);
+  __syncthreads();
+
+  const long long lo = L.row_lo[gt], n = L.row_hi[gt] - lo;
+  const long long r_lo = lo + (n * part) / n_part, r_hi = lo + (n * (part + 1)) / n_part;
+  const size_t stride = (size_t)n_ant * NV + 1;
+  double* Pc = partials + ((size_t)interval * n_part + part) * stride;
+  const cx<T>* tab = reinterpret_cast<const cx<T>*>(L.band_gains) + ((size_t)gt * n_slices + slice) * n_ant * 2 * CW;
+  const S* Dp = reinterpret_cast<const S*>(V.data);
+  const S* Mp = reinterpret_cast<const S*>(V.model);
+  const S* Wp = reinterpret_cast<const S*>(V.weight);
+
+  bool first = true;          // no FP64 flush yet: the first one stores
+  A chi = A(0);
+  double chi64 = 0.0;
+  A pacc[NV];
+#pragma unroll
+  for (int k = 0; k < NV; ++k) pacc[k] = A(0);
+  int p_cur = -1, t_cur = -1;
+
+  // the sums of the lanes whose antenna p is over (`over`) into LDS, one row of
+  // the step after the other (several rows usually share the antenna)
+  auto flush_p = [&](bool over) {
+    const bool add = over && p_cur >= 0 && cin;
+    band_add_turns<A, CW>(add, g, p_cur, cl, pacc);
+#pragma unroll
+    for (int k = 0; k < NV; ++k) pacc[k] = over ? A(0) : pacc[k];
+  };
+  // the LDS slots added into the part's FP64 blocks, and cleared; the blocks of
+  // earlier times are read eight at a time
+  auto flush_lds = [&]() {
+    __syncthreads();
+    constexpr int U = 8;
+    const int n_av = n_ant * NV;
+    for (int i0 = g; i0 < n_av; i0 += NR * U) {      // (antenna, value)
+      double x[U], was[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int i = i0 + NR * u;
+        x[u] = 0.0;
+        was[u] = 0.0;
+        if (i < n_av) {
+          A* ps = band_slot<A, CW>(i / NV, i % NV, cl);
+          x[u] = (double)*ps;
+          *ps = A(0);
+          if (!first && cin) was[u] = Pc[i];
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int i = i0 + NR * u;
+        if (i < n_av && cin) Pc[i] = was[u] + x[u];
+      }
+    }
+    __syncthreads();
+    chi64 += (double)chi;
+    chi = A(0);
+    first = false;
+  };
+
+  // row of this lane in the step that begins at row r (clamped into the part)
+  auto row_at = [&](long long r) -> long long { return min(r + g, r_hi - 1); };
+  auto load_row = [&](long long r) -> BandRow<T> {
+    const long long rr = row_at(r);
+    BandRow<T> a{V.ant1[rr], V.ant2[rr], V.row_time[rr]};
+    const bool ok = r + g < r_hi && a.p != a.q && (unsigned)a.p < (unsigned)n_ant && (unsigned)a.q < (unsigned)n_ant;
+    a.p = ok ? a.p : 0;
+    a.q = ok ? a.q : -1;
+    return a;
+  };
+  auto load_gain = [&](const BandRow<T>& a) -> BandGain<T> {
+    const cx<T>* hp = tab + (size_t)a.p * 2 * CW + cl;
+    const cx<T>* hq = tab + (size_t)max(a.q, 0) * 2 * CW + cl;
+    return {hp[0], hp[CW], hq[0], hq[CW]};
+  };
+  RawSample<S> x0 = {}, x1 = {}, x2 = {};
+  BandRow<T> a0{0, -1, 0}, a1{0, -1, 0}, a2{0, -1, 0};
+  BandGain<T> h0 = {}, h1 = {};
+  auto load_x = [&](RawSample<S>& x, long long r) {
+    raw_load<S>(x, Dp, Mp, Wp, V.flag, (size_t)row_at(r) * n_chan + cc, V.n_wcorr);
+  };
+  if (r_lo < r_hi) {
+    load_x(x0, r_lo);
+    a0 = load_row(r_lo);
+    load_x(x1, r_lo + NR);
+    a1 = load_row(r_lo + NR);
+    h0 = load_gain(a0);
+  }
+  for (long long r = r_lo; r < r_hi; r += NR) {
+    load_x(x2, r + 2 * NR);
+    a2 = load_row(r + 2 * NR);
+    h1 = load_gain(a1);
+    // the time of the step's first row
+    const int t = __builtin_amdgcn_readfirstlane(a0.t);
+    if (t != t_cur) {
+      if (t_cur >= 0) {
+        flush_p(true);
+        p_cur = -1;
+        flush_lds();
+      }
+      t_cur = t;
+    }
+    const bool row_ok = a0.q >= 0;
+    const bool over = row_ok && a0.p != p_cur;
+    if (__any(over)) {
+      flush_p(over);
+      p_cur = over ? a0.p : p_cur;
+    }
+    T w0, w1, w2, w3;
+    raw_weights<S, T>(x0, V.n_wcorr, w0, w1, w2, w3);
+    const bool use = row_ok & cin & (x0.f == 0);
+    w0 = use ? w0 : T(0); w1 = use ? w1 : T(0); w2 = use ? w2 : T(0); w3 = use ? w3 : T(0);
+    const m22<T> D = select_m(use, raw_data<T>(x0));
+    const m22<T> E = select_m(use, raw_model<T>(x0));
+    m22<T> B, Bc;
+    B.a = mulc(E.a, h0.q0);
+    B.b = mulc(E.b, h0.q1);
+    B.c = mulc(E.c, h0.q0);
+    B.d = mulc(E.d, h0.q1);
+    Bc.a = conj(E.a * h0.p0);
+    Bc.b = conj(E.c * h0.p1);
+    Bc.c = conj(E.b * h0.p0);
+    Bc.d = conj(E.d * h0.p1);
+    const m22<T> R = D - rowscale(h0.p0, h0.p1, B);
+    const m22<T> WR = wmul(R, w0, w1, w2, w3);
+    A qv[NV];
+#pragma unroll
+    for (int k = 0; k < NV; ++k) qv[k] = A(0);
+    contrib<KIND_DIAG, true, T>(cone<T>(), cone<T>(), B, WR, w0, w1, w2, w3, h0.p0, h0.p1, T(1), pacc);
+    contrib<KIND_DIAG, true, T>(cone<T>(), cone<T>(), Bc, herm(WR), w0, w2, w1, w3, h0.q0, h0.q1, T(1), qv);
+    chi = chisq_acc(WR, R, chi);
+
+    // two rows of the step that share antenna q are added one after the other
+    const int q_own = row_ok ? a0.q : -1 - g;
+    bool dup = false;
+#pragma unroll
+    for (int h = 1; h < NR; ++h) dup = dup || __shfl_xor(q_own, h * CW) == q_own;
+    const bool add = row_ok && cin;
+    if (!__any(dup)) {
+      if (add) band_add<A, CW>(a0.q, cl, qv);
+      band_turn();
+    } else {
+      band_add_turns<A, CW>(add, g, a0.q, cl, qv);
+    }
+    x0 = x1;
+    x1 = x2;
+    a0 = a1;
+    a1 = a2;
+    h0 = h1;
+  }
+  flush_p(true);
+  flush_lds();
+  // chi^2 of the channel: the sums of the step's rows
+  double cs = chi64;
+  cs = band_full<32>(cs);
+  cs = band_full<16>(cs);
+  if constexpr (CW == 8) cs = band_full<8>(cs);
+  if (g == 0 && cin) Pc[stride - 1] = cs;
+}
+
+// One pass of that kernel, its gain table first.
+template <typename S, typename T, int CW>
+hipError_t launch_band_single(const SolveLaunch& L, int n_part, double* partials, const uint8_t* done, unsigned grid,
+                              size_t lds, hipStream_t stream) {
+  const TermArgs& ta = L.chain.t[L.chain.active];
+  const int n_slices = (L.vis.n_chan + CW - 1) / CW;
+  const size_t n = (size_t)ta.n_gt * n_slices * L.vis.n_ant * 2 * CW;
+  hipLaunchKernelGGL((k_band_gains<T, CW>), dim3((unsigned)((n + 255) / 256)), dim3(256), 0, stream,
+                     (const double2*)L.gains, ta.n_gf, L.vis.n_ant, n_slices, n, reinterpret_cast<cx<T>*>(L.band_gains));
+  hipLaunchKernelGGL((k_band_single<S, T, CW>), dim3(grid), dim3(64), lds, stream, L, n_part, partials, done);
+  return hipGetLastError();
 }
 
 }  // namespace

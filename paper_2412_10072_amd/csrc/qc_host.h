@@ -28,9 +28,10 @@ constexpr double SPLIT_PART_SAMPLES = 32768.0;
 constexpr double SPLIT_MIN_SAMPLES = 512.0;
 constexpr double SPLIT_MIN_ROWS = 16.0;
 // Wavefronts per compute unit that the split over one-channel intervals aims
-// at (each holds 16 intervals and 24 KiB of LDS at 64 antennas, so about six
-// are resident per CU: two rounds of them; 6 to 48 measured within 6%)
-constexpr int BAND_WAVES_PER_CU = 12;
+// at: one round of as many as the LDS holds (24 KiB each at 64 antennas and FP32:
+// six), at most two per SIMD for the registers.  512 channels x 100 times: 6 per
+// CU 51.8 ms a solve, 4 61.7, 8 71.8, 12 54.2, 24 64.1.
+constexpr int BAND_WAVES_PER_CU = 8;
 
 struct qc_ctx {
   int device = 0;
@@ -107,6 +108,8 @@ struct qc_ctx {
   size_t acc_cap = 0;
   qc::BandStep* d_band = nullptr;        // split schedule over one-channel intervals: steps per row
   size_t band_cap = 0;
+  unsigned char* d_bandg = nullptr;    // that split: gains in the order of its steps
+  size_t bandg_cap = 0;
   unsigned char* d_ddtab = nullptr;    // that split: tables of the direction-dependent fixed terms
   size_t ddtab_cap = 0;
   int last_split_parts = 1;   // parts per interval of the last solve (1 = fused)

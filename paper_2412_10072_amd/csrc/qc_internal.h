@@ -407,6 +407,7 @@ struct SolveLaunch {
   int dir_ident;
   const BandStep* band_steps;
   int band_rows;              // rows per step of that pass: 4 or 8
+  void* band_gains;           // its gain table where the chain is the active term over one direction, else null
   // diagonal chains (every pass, the band pass included) whose
   // direction-dependent fixed terms are all diagonal, at most BAND_MAX_DD of
   // them: dd_tabled, and those terms (chain indices) each as a table
@@ -425,6 +426,8 @@ hipError_t launch_band_steps(const SolveLaunch& L, int n_part, int rows, BandSte
 // LDS bytes of that pass for n_ant antennas (FP32 or FP64 sums) and `rows`
 // rows per step (64 / rows channels per wavefront)
 size_t band_lds_bytes_for(int n_ant, bool fp32, int rows);
+// bytes of that pass's gain table (the active term alone over one direction)
+size_t band_gains_bytes(const SolveLaunch& L);
 // Table of direction-dependent fixed term j (diagonal gains) for that pass:
 // bytes needed, and the fill on `stream`.
 size_t dd_table_bytes(const SolveLaunch& L, int j);

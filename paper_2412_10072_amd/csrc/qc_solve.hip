@@ -305,6 +305,12 @@ size_t band_lds_bytes_for(int n_ant, bool fp32, int rows) {
   return (fp32 ? sizeof(float) : sizeof(double)) * (size_t)n_ant * KindInfo<KIND_DIAG>::NV * (64 / rows);
 }
 
+size_t band_gains_bytes(const SolveLaunch& L) {
+  const TermArgs& ta = L.chain.t[L.chain.active];
+  const size_t cw = 64 / L.band_rows, slices = (L.vis.n_chan + cw - 1) / cw;
+  return (size_t)ta.n_gt * slices * cw * L.vis.n_ant * 2 * (L.prec_mixed ? sizeof(cx<float>) : sizeof(cx<double>));
+}
+
 hipError_t launch_band_steps(const SolveLaunch& L, int n_part, int rows, BandStep* steps, hipStream_t stream) {
   if (rows != 4 && rows != 8) return hipErrorInvalidValue;
   const TermArgs& ta = L.chain.t[L.chain.active];

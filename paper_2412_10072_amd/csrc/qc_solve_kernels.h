@@ -311,6 +311,13 @@ hipError_t launch_band(const SolveLaunch& L, const SplitLaunch& P, hipStream_t s
     const long long grid = (long long)((L.vis.n_chan + cw - 1) / cw) * ta.n_gt * P.n_part;
     if (grid > 0x7fffffffLL) return hipErrorInvalidValue;
     const uint8_t* done = P.state.done;
+    if (L.band_gains) {
+      const hipError_t e = L.band_rows == 8
+          ? launch_band_single<S, T, 8>(L, P.n_part, P.partials, done, (unsigned)grid, lds, stream)
+          : launch_band_single<S, T, 16>(L, P.n_part, P.partials, done, (unsigned)grid, lds, stream);
+      if (e != hipSuccess) return e;
+      return launch_split_update(ku, L, P, (size_t)L.vis.n_ant * BAND_NV + 1, lds_u, stream);
+    }
     void (*kern)(SolveLaunch, int, double*, const uint8_t*) = nullptr;
     if (L.band_rows == 8) {
       kern = L.n_dd == 0 ? k_band_pass<S, T, 0, 8> : L.n_dd == 1 ? k_band_pass<S, T, 1, 8> : k_band_pass<S, T, 2, 8>;
@@ -410,7 +417,7 @@ hipError_t launch_kind(const SolveLaunch& L, const SplitLaunch* P, hipStream_t s
   const TermArgs& ta = ch.t[ch.active];
   if (L.sky.comp) return launch_kind_sky<KIND, S, T>(L, P, stream, lds_out);
   if constexpr (KIND == KIND_DIAG) {
-    if (P && L.band_steps) return launch_band<S, T>(L, *P, stream, lds_out);
+    if (P && (L.band_steps || L.band_gains)) return launch_band<S, T>(L, *P, stream, lds_out);
   }
   if constexpr (KIND != KIND_DELOFF) {          // (the host offers no LM for delay-and-offset terms)
     if (L.damping == DAMP_LM && !P) return launch_kind_lm<KIND, S, T>(L, stream, lds_out);
