@@ -362,6 +362,7 @@ qc_status qc_ctx_destroy(qc_ctx* ctx) {
   hipFree(ctx->d_acc);
   hipFree(ctx->d_band);
   hipFree(ctx->d_bandg);
+  hipFree(ctx->d_ptab);
   hipFree(ctx->d_ddtab);
   hipEventDestroy(ctx->ev0);
   hipEventDestroy(ctx->ev1);
@@ -446,19 +447,19 @@ static int split_parts(const qc_ctx* ctx, const qc_vis* vis, const qc_term& ta, 
   return blocks * 24.0 * sizeof(double) > 2147483648.0 ? 1 : parts;
 }
 
-// Memory for a folded model in the context: at most a sixteenth of the device's,
+// Memory of the context that a solve can do without: at most a sixteenth of the device's,
 // and, when it has to grow, an eighth of what is free (the arrays the caller
 // may still want come first); false: the solve goes without.
-static bool fold_memory(qc_ctx* ctx, size_t bytes) {
+static bool spare_memory(qc_ctx* ctx, unsigned char*& ptr, size_t& cap, size_t bytes) {
   if (bytes == 0) return false;
-  if (ctx->d_fold && bytes <= ctx->fold_cap) return true;
+  if (ptr && bytes <= cap) return true;
   size_t free_b = 0, total_b = 0;
   if (hipMemGetInfo(&free_b, &total_b) != hipSuccess) {
     (void)hipGetLastError();
     return false;
   }
   if (bytes > total_b / 16 || bytes > free_b / 8) return false;
-  if (grow(ctx->d_fold, ctx->fold_cap, bytes) == hipSuccess) return true;
+  if (grow(ptr, cap, bytes) == hipSuccess) return true;
   (void)hipGetLastError();
   return false;
 }
@@ -569,7 +570,7 @@ static qc_status solve_interval_impl(qc_ctx* ctx, const qc_vis* vis, qc_term* ch
   // the one-row-per-lane kernel of chains.)
   bool fold = !fixed && !sky && !lm && L.diag_chain && !single_chain && ta.n_gdir == 1 && opts->max_iter >= 3 &&
               L.prec_mixed != L.vis_is_c128 && (one_chan || ctx->max_int_chan > 4);
-  if (fold) fold = fold_memory(ctx, chain_fold_bytes(L));
+  if (fold) fold = spare_memory(ctx, ctx->d_fold, ctx->fold_cap, chain_fold_bytes(L));
   if (lm && ta.type == QC_TERM_DELAY_OFFSET)
     return fail(ctx, QC_E_UNSUPPORTED, "Levenberg-Marquardt takes no delay-and-offset term");
   if (fixed) {
@@ -662,6 +663,12 @@ static qc_status solve_interval_impl(qc_ctx* ctx, const qc_vis* vis, qc_term* ch
     }
   }
   size_t dd_off[BAND_MAX_DD] = {0, 0};
+  L.ptab = nullptr;
+  if (parts > 1 && (single_chain || fold) && !sky && !L.prec_mixed &&
+      (ta.type == QC_TERM_DELAY || ta.type == QC_TERM_DELAY_OFFSET)) {
+    const size_t bytes = sizeof(double) * 4 * (size_t)n_int * vis->n_ant * ctx->max_int_chan;
+    if (spare_memory(ctx, ctx->d_ptab, ctx->ptab_cap, bytes)) L.ptab = ctx->d_ptab;
+  }
   L.band_gains = nullptr;
   if (band && (fold || single_chain)) {
     HIP_TRY(ctx, grow(ctx->d_bandg, ctx->bandg_cap, band_gains_bytes(L)));

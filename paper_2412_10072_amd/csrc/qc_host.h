@@ -108,6 +108,8 @@ struct qc_ctx {
   size_t acc_cap = 0;
   qc::BandStep* d_band = nullptr;        // split schedule over one-channel intervals: steps per row
   size_t band_cap = 0;
+  unsigned char* d_ptab = nullptr;     // split schedule: phasors of an FP64 delay term
+  size_t ptab_cap = 0;
   unsigned char* d_bandg = nullptr;    // that split: gains in the order of its steps
   size_t bandg_cap = 0;
   unsigned char* d_ddtab = nullptr;    // that split: tables of the direction-dependent fixed terms

@@ -405,6 +405,7 @@ struct SolveLaunch {
   // gain direction d of the active term (n_gdir = n_dir <= 4): the kernels of
   // the CHAIN_DIAG_ID mode
   int dir_ident;
+  void* ptab;                 // split passes of FP64 delay terms: phasor table (Job::ptab), or null
   const BandStep* band_steps;
   int band_rows;              // rows per step of that pass: 4 or 8
   void* band_gains;           // its gain table where the chain is the active term over one direction, else null

@@ -924,6 +924,10 @@ struct Job {
   int n_dd;
   int dd_term[BAND_MAX_DD];
   const void* dd_tab[BAND_MAX_DD];
+  // split passes of FP64 delay terms: the phasors of every (interval, antenna,
+  // channel of the interval, hand) [..][n_ant][ptab_w][2], or null (formed per sample)
+  const void* ptab;
+  int ptab_w;
 };
 
 // The largest frequency of channels [c_lo, c_hi): band_top_part by every
@@ -1322,6 +1326,10 @@ __device__ __forceinline__ void solve_interval(const Job& J) {
   const TermArgs& TA = *J.TA;
   const int pk = TA.kind;                    // delay / phase / amplitude for KIND_DELAY
   const bool pk_amp = (KIND == KIND_DELAY) && pk == KIND_AMP;
+  constexpr bool FLAT_GAIN = KIND == KIND_DELAY && (SINGLE || DIAGC);
+  const bool pk_flat = FLAT_GAIN && (pk == KIND_PHASE || pk == KIND_AMP);
+  // FP64 delay phasors of a split pass from its table (k_param_table)
+  constexpr bool PHASOR_TAB = is_param(KIND) && SINGLE && PASS_ONLY && !SKY && sizeof(T) == 8;
   const int n_ant = V.n_ant;
   const int n_gdir = SINGLE ? 1 : TA.n_gdir;
   const int gt = J.gt, gf = J.gf, n_gf = J.n_gf;
@@ -1440,6 +1448,20 @@ __device__ __forceinline__ void solve_interval(const Job& J) {
   };
 
   for (int it = 0;; ++it) {
+    if constexpr (FLAT_GAIN) {
+      // phase-only and amplitude gains do not depend on the frequency: formed
+      // once per pass and block, read from LDS per sample as complex gains are
+      // (phase-only solve, 64 antennas, 40 times x 512 channels, intervals of 1 x
+      // 64: FP64 8.07 -> 5.45 ms, MIXED 5.36 -> 4.76)
+      if (pk_flat) {
+        for (int i = threadIdx.x; i < n_ant * n_gdir; i += blockDim.x) {
+          const int ant = i / n_gdir, slot = ant * NG + (i - ant * n_gdir);
+          gc[slot * 4 + 0] = param_gain<T>(pk, 0.0, gm[slot * 4].x);
+          gc[slot * 4 + 3] = param_gain<T>(pk, 0.0, gm[slot * 4].y);
+        }
+        __syncthreads();
+      }
+    }
     for (int i = lane; i < slot_vals; i += 64) {
       my_s[i] = A(0);
       if constexpr (KAHAN) my_c[i] = A(0);
@@ -1537,6 +1559,18 @@ __device__ __forceinline__ void solve_interval(const Job& J) {
         T w0, w1, w2, w3;
         uint8_t fl;
         m22<T> Draw, Mpf;
+        // the antennas' phasors, before the loads of the next chunk (which are
+        // not waited for)
+        cx<T> tabp[2] = {cone<T>(), cone<T>()}, tabq[2] = {cone<T>(), cone<T>()};
+        if constexpr (PHASOR_TAB) {
+          if (J.ptab) {
+            const cx<T>* tb = reinterpret_cast<const cx<T>*>(J.ptab) + ((size_t)interval * n_ant * J.ptab_w + (cc - c_lo)) * 2;
+            const cx<T>* ep = tb + (size_t)p * J.ptab_w * 2;
+            const cx<T>* eq = tb + (size_t)q * J.ptab_w * 2;
+            tabp[0] = ep[0]; tabp[1] = ep[1];
+            tabq[0] = eq[0]; tabq[1] = eq[1];
+          }
+        }
         if constexpr (PF) {
           // this chunk's values were loaded during the last one; the loads of
           // the next chunk of this step (else the first chunk of the next
@@ -1582,8 +1616,20 @@ __device__ __forceinline__ void solve_interval(const Job& J) {
           if constexpr (is_param(KIND)) {
             Gp = mzero<T>();
             Gq = mzero<T>();
-            param_diag<KIND, T>(gm + p * 4, pk, nu, Gp.a, Gp.d);
-            param_diag<KIND, T>(gm + q * 4, pk, nu, Gq.a, Gq.d);
+            if (pk_flat) {
+              Gp.a = gc[p * 4];
+              Gp.d = gc[p * 4 + 3];
+              Gq.a = gc[q * 4];
+              Gq.d = gc[q * 4 + 3];
+            } else if (PHASOR_TAB && J.ptab) {
+              Gp.a = tabp[0];
+              Gp.d = tabp[1];
+              Gq.a = tabq[0];
+              Gq.d = tabq[1];
+            } else {
+              param_diag<KIND, T>(gm + p * 4, pk, nu, Gp.a, Gp.d);
+              param_diag<KIND, T>(gm + q * 4, pk, nu, Gq.a, Gq.d);
+            }
           } else {
             Gp = {gc[p * 4 + 0], gc[p * 4 + 1], gc[p * 4 + 2], gc[p * 4 + 3]};
             Gq = {gc[q * 4 + 0], gc[q * 4 + 1], gc[q * 4 + 2], gc[q * 4 + 3]};
@@ -1634,7 +1680,7 @@ __device__ __forceinline__ void solve_interval(const Job& J) {
           }
           // active gains of p and q for gain direction gd
           auto active_diag = [&](int gd, cx<T>& a0, cx<T>& a1, cx<T>& b0, cx<T>& b1) {
-            if constexpr (is_param(KIND)) {
+            if (is_param(KIND) && !pk_flat) {
               param_diag<KIND, T>(gm + (p * NG + gd) * 4, pk, nu, a0, a1);
               param_diag<KIND, T>(gm + (q * NG + gd) * 4, pk, nu, b0, b1);
             } else {
