@@ -22,6 +22,7 @@
 
 #include <cmath>
 #include <cstring>
+#include <type_traits>
 
 #include "qc_host.h"
 #include "qc_hostcheck.h"
@@ -124,16 +125,14 @@ template <typename S> struct alignas(4 * sizeof(S)) Weight4 {
 
 // vec_r / vec_w: the residual / weights are aligned for whole-sample loads
 template <typename S>
-__device__ __forceinline__ S sample_stat(const S* R, const S* W, int n_wcorr, bool vec_r, bool vec_w, size_t s) {
-#pragma clang fp contract(off)
-  Resid4<S> r;
+__device__ __forceinline__ void stat_load(const S* R, const S* W, int n_wcorr, bool vec_r, bool vec_w, size_t s,
+                                          Resid4<S>& r, Weight4<S>& w) {
   if (vec_r) {
     r = reinterpret_cast<const Resid4<S>*>(R)[s];
   } else {
 #pragma unroll
     for (int j = 0; j < 8; ++j) r.v[j] = R[8 * s + j];
   }
-  Weight4<S> w;
   if (n_wcorr == 4 && vec_w) {
     w = reinterpret_cast<const Weight4<S>*>(W)[s];
   } else if (n_wcorr == 4) {
@@ -143,6 +142,11 @@ __device__ __forceinline__ S sample_stat(const S* R, const S* W, int n_wcorr, bo
     const S w0 = W[s];
     w.v[0] = w.v[1] = w.v[2] = w.v[3] = w0;
   }
+}
+
+template <typename S>
+__device__ __forceinline__ S stat_value(const Resid4<S>& r, const Weight4<S>& w) {
+#pragma clang fp contract(off)
   S acc = S(0);
 #pragma unroll
   for (int k = 0; k < 4; ++k) {
@@ -234,12 +238,26 @@ __global__ void __launch_bounds__(FL_THREADS) k_fl_stat(FlagArgs A) {
     __syncthreads();
     mine = 0;
   };
-  auto one = [&](size_t e, bool live) {
-    const uint8_t f = A.vis.flag[e];
-    const S v = sample_stat<S>(R, W, A.vis.n_wcorr, A.vec_r, A.vec_w, e);
-    const bool use = live && f == 0 && isfinite(v);   // non-finite statistics take no part
-    out[e] = use ? v : S(-1);
-    mine += use ? 1 : 0;
+  // NR rows' samples at one channel, all of them loaded before any is written
+  // (the store of one would hold back the loads of the next)
+  auto some = [&](auto nr, const long long* rows, int c, bool live) {
+    constexpr int NR = decltype(nr)::value;
+    Resid4<S> x[NR];
+    Weight4<S> w[NR];
+    uint8_t f[NR];
+#pragma unroll
+    for (int j = 0; j < NR; ++j) {
+      const size_t e = (size_t)rows[j] * n_chan + c;
+      f[j] = A.vis.flag[e];
+      stat_load<S>(R, W, A.vis.n_wcorr, A.vec_r, A.vec_w, e, x[j], w[j]);
+    }
+#pragma unroll
+    for (int j = 0; j < NR; ++j) {
+      const S v = stat_value<S>(x[j], w[j]);
+      const bool use = live && f[j] == 0 && isfinite(v);   // non-finite statistics take no part
+      out[(size_t)rows[j] * n_chan + c] = use ? v : S(-1);
+      mine += use ? 1 : 0;
+    }
   };
   long long i = i0;
   while (i < i1) {                   // i, r, g: uniform over the workgroup
@@ -253,17 +271,13 @@ __global__ void __launch_bounds__(FL_THREADS) k_fl_stat(FlagArgs A) {
     if (i + 4 <= i1) {               // four rows of one group in flight
       const long long r1 = list_row(A, i + 1), r2 = list_row(A, i + 2), r3 = list_row(A, i + 3);
       if (group_of(A, r1) == g && group_of(A, r2) == g && group_of(A, r3) == g) {
-        for (int c = threadIdx.x; c < n_chan; c += FL_THREADS) {
-          one((size_t)r * n_chan + c, live);
-          one((size_t)r1 * n_chan + c, live);
-          one((size_t)r2 * n_chan + c, live);
-          one((size_t)r3 * n_chan + c, live);
-        }
+        const long long rows[4] = {r, r1, r2, r3};
+        for (int c = threadIdx.x; c < n_chan; c += FL_THREADS) some(std::integral_constant<int, 4>{}, rows, c, live);
         i += 4;
         continue;
       }
     }
-    for (int c = threadIdx.x; c < n_chan; c += FL_THREADS) one((size_t)r * n_chan + c, live);
+    for (int c = threadIdx.x; c < n_chan; c += FL_THREADS) some(std::integral_constant<int, 1>{}, &r, c, live);
     ++i;
   }
   if (cur >= 0) flush();
@@ -387,14 +401,23 @@ __global__ void __launch_bounds__(64) k_fl_select(FlagArgs A, int last) {
   GroupState& G = A.gs[g];
   if (G.n <= 0) return;
   const int lane = threadIdx.x;
-  const unsigned* hg = A.hist + (size_t)g * NBIN;
-  const int nb = 1 << A.bits;
-  const int per = (nb + 63) / 64;
-  long long mine = 0;
-  for (int j = 0; j < per; ++j) {
-    const int b = lane * per + j;
-    if (b < nb) mine += hg[b];
+  // a lane's bins, 16 bytes at a time, and cleared for the next digit (a fill of
+  // all histograms before each digit took 8.5 us for 2016 groups)
+  constexpr int PER = NBIN / 64;
+  uint4* hg = reinterpret_cast<uint4*>(A.hist + (size_t)g * NBIN) + (size_t)lane * (PER / 4);
+  unsigned c[PER];
+#pragma unroll
+  for (int j = 0; j < PER / 4; ++j) {
+    const uint4 v = hg[j];
+    hg[j] = make_uint4(0u, 0u, 0u, 0u);
+    c[4 * j] = v.x;
+    c[4 * j + 1] = v.y;
+    c[4 * j + 2] = v.z;
+    c[4 * j + 3] = v.w;
   }
+  long long mine = 0;
+#pragma unroll
+  for (int j = 0; j < PER; ++j) mine += c[j];
   // inclusive prefix over lanes (fixed order)
   long long incl = mine;
   for (int o = 1; o < 64; o <<= 1) {
@@ -408,15 +431,14 @@ __global__ void __launch_bounds__(64) k_fl_select(FlagArgs A, int last) {
   const int owner = ball ? __builtin_ctzll(ball) : 63;
   if (lane == owner) {
     long long run = excl;
-    int digit = lane * per;
-    for (int j = 0; j < per; ++j) {
-      const int b = lane * per + j;
-      const long long c = b < nb ? hg[b] : 0;
-      if (rank < run + c) {
-        digit = b;
-        break;
-      }
-      run += c;
+    int digit = lane * PER;
+    bool found = false;
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+      const bool hit = !found && rank < run + (long long)c[j];
+      digit = hit ? lane * PER + j : digit;
+      found = found || hit;
+      run += found ? 0 : (long long)c[j];
     }
     const U sel = (U)digit << A.shift;
     const U dm = (U)((1u << A.bits) - 1u) << A.shift;
@@ -533,13 +555,14 @@ hipError_t run_flag(FlagArgs A, int* count, int* off, int* cursor, int* rowlist,
   const unsigned lb = (unsigned)((n_row + FL_ROWS - 1) / FL_ROWS);
   if (lb > 0) hipLaunchKernelGGL(k_fl_stat<S>, dim3(lb), dim3(FL_THREADS), 0, s, A);
   constexpr int BITS = KeyT<S>::BITS;
+  // (each selection leaves its histograms cleared)
+  hipLaunchKernelGGL(k_fl_fill, dim3(1024), dim3(256), 0, s, A.hist, (size_t)A.n_groups * NBIN, 0u);
   for (int phase = 0; phase < 2; ++phase) {
     A.phase = phase;
     hipLaunchKernelGGL(k_fl_rank, dim3((A.n_groups + 255) / 256), dim3(256), 0, s, A.gs, A.n_groups);
     for (int hi = BITS; hi > 0; hi -= DIGIT) {
       A.bits = hi >= DIGIT ? DIGIT : hi;
       A.shift = hi - A.bits;
-      hipLaunchKernelGGL(k_fl_fill, dim3(1024), dim3(256), 0, s, A.hist, (size_t)A.n_groups * NBIN, 0u);
       if (lb > 0) hipLaunchKernelGGL(k_fl_hist<S>, dim3(lb), dim3(FL_THREADS), 0, s, A);
       hipLaunchKernelGGL(k_fl_select<S>, dim3(A.n_groups), dim3(64), 0, s, A, A.shift == 0 ? 1 : 0);
     }

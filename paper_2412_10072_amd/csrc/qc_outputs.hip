@@ -91,6 +91,13 @@ __device__ __forceinline__ void diag_part(const ChainArgs& CH, int n_ant, int t,
   }
 }
 
+// |c|^2 with its rounding spelled out, so that every form of the weights below
+// gives the same bits.
+template <typename T>
+__device__ __forceinline__ T gain_power(cx<T> c) {
+  return fma(c.re, c.re, c.im * c.im);
+}
+
 // w |c_p,i|^2 |c_q,j|^2 into the weights of sample s (one weight: the mean factor)
 // (vec: four weights per sample, both arrays 16-byte aligned: one vector load
 // and store per sample, the same products)
@@ -98,7 +105,7 @@ template <typename S, typename T>
 __device__ __forceinline__ void corrected_weight(const VisArgs& V, size_t s, cx<T> p0, cx<T> p1, cx<T> q0,
                                                  cx<T> q1, S* out, bool vec) {
   const S* W = reinterpret_cast<const S*>(V.weight);
-  const T a0 = norm2(p0), a1 = norm2(p1), b0 = norm2(q0), b1 = norm2(q1);
+  const T a0 = gain_power(p0), a1 = gain_power(p1), b0 = gain_power(q0), b1 = gain_power(q1);
   const T f[4] = {a0 * b0, a0 * b1, a1 * b0, a1 * b1};
   if (V.n_wcorr == 4 && vec) {
     if constexpr (sizeof(S) == 4) {
@@ -246,6 +253,59 @@ __global__ void __launch_bounds__(256) k_outputs(OutputLaunch L) {
     }
   };
   const long long first = (long long)blockIdx.x * nw + wave, step = (long long)gridDim.x * nw;
+  if constexpr (MODE == 3 && !FLAT) {
+    // corrected weights, four per sample: a row's weights of four steps are read
+    // before the first is written (the chain and the store of one step would
+    // hold back the read of the next; 64 antennas, 50 x 1024: 803 -> 675 us)
+    if (L.w_vec) {
+      using W4 = S __attribute__((ext_vector_type(4)));
+      const W4* Wp = reinterpret_cast<const W4*>(V.weight);
+      W4* Ow = reinterpret_cast<W4*>(L.out);
+      constexpr int U = 4;
+      for (long long r = first; r < V.n_row; r += step) {
+        const int p = V.ant1[r], q = V.ant2[r], t = V.row_time[r];
+        if ((unsigned)p >= (unsigned)V.n_ant || (unsigned)q >= (unsigned)V.n_ant) continue;
+        for (int c0 = lane; c0 < V.n_chan; c0 += 64 * U) {
+          W4 w[U];
+#pragma unroll
+          for (int u = 0; u < U; ++u) w[u] = Wp[(size_t)r * V.n_chan + min(c0 + 64 * u, V.n_chan - 1)];
+#pragma unroll
+          for (int u = 0; u < U; ++u) {
+            const int c = c0 + 64 * u;
+            if (c >= V.n_chan) break;
+            const double nu = V.freq[c];
+            cx<T> p0, p1, q0, q1;
+            if constexpr (TAB) {
+              constexpr int E = DIAG ? 2 : 4;
+              const cx<T>* tp = tab + (((size_t)t * V.n_ant + p) * V.n_chan + c) * E;
+              const cx<T>* tq = tab + (((size_t)t * V.n_ant + q) * V.n_chan + c) * E;
+              p0 = tp[0]; p1 = tp[E - 1];
+              q0 = tq[0]; q1 = tq[E - 1];
+              if constexpr (DIAG) {
+                diag_part<T, true>(CH, V.n_ant, t, c, p, 0, nu, p0, p1);
+                diag_part<T, true>(CH, V.n_ant, t, c, q, 0, nu, q0, q1);
+              }
+            } else if constexpr (DIAG) {
+              p0 = p1 = q0 = q1 = cone<T>();
+              diag_part<T, false>(CH, V.n_ant, t, c, p, 0, nu, p0, p1);
+              diag_part<T, false>(CH, V.n_ant, t, c, q, 0, nu, q0, q1);
+              diag_part<T, true>(CH, V.n_ant, t, c, p, 0, nu, p0, p1);
+              diag_part<T, true>(CH, V.n_ant, t, c, q, 0, nu, q0, q1);
+            } else {
+              const m22<T> Cp = chain_range<T>(CH, V.n_ant, 0, CH.n_term, t, c, p, 0, nu);
+              const m22<T> Cq = chain_range<T>(CH, V.n_ant, 0, CH.n_term, t, c, q, 0, nu);
+              p0 = Cp.a; p1 = Cp.d;
+              q0 = Cq.a; q1 = Cq.d;
+            }
+            const T a0 = gain_power(p0), a1 = gain_power(p1), b0 = gain_power(q0), b1 = gain_power(q1);
+            Ow[(size_t)r * V.n_chan + c] = W4{w[u][0] * (a0 * b0), w[u][1] * (a0 * b1), w[u][2] * (a1 * b0),
+                                              w[u][3] * (a1 * b1)};
+          }
+        }
+      }
+      return;
+    }
+  }
   if constexpr (FLAT) {
     const long long n = V.n_row * V.n_chan;
     for (long long s0 = first * 64; s0 < n; s0 += step * 64) {

@@ -1,0 +1,73 @@
+"""Robust weights, corrected weights and the flagging statistic at the edges of
+their steps (channel counts around 64, 128 and 256) and of alignment (arrays
+that begin off a 16-byte boundary take narrower reads): bitwise equal to the
+aligned arrays' results where only the reads differ, and against the oracle."""
+import sys
+
+import numpy as np
+import pytest
+import torch
+
+from helpers import make_term, make_vis, rand_c
+from oracle import flagging as o_flag
+from oracle import robust as o_rob
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+def say(msg):
+    print(msg, flush=True)
+    sys.stdout.flush()
+
+
+def shifted(t):
+    """The same values, one element (of the weight or complex type) off."""
+    flat = torch.empty(t.numel() + 1, dtype=t.dtype, device=t.device)[1:]
+    flat.copy_(t.reshape(-1))
+    return flat.view(t.shape)
+
+
+@pytest.mark.parametrize("dtype", ["c64", "c128"])
+@pytest.mark.parametrize("n_wcorr", [1, 4])
+@pytest.mark.parametrize("n_chan", [1, 63, 65, 130, 257])
+def test_weights_and_flags(qc_lib, n_chan, n_wcorr, dtype):
+    from paper_2412_10072_amd import qc
+    say(f"weights {n_chan} channels, {n_wcorr} weights, {dtype}")
+    rng = np.random.default_rng(n_chan)
+    vis = make_vis(rng, n_ant=5, n_time=4, n_chan=n_chan, n_wcorr=n_wcorr)
+    term = make_term(rng, "diag", 4, n_chan, 5, t_int=2, f_int=40, scale=0.2)
+    resid = 0.1 * rand_c(rng, *vis.data.shape)
+    resid[rng.random(resid.shape[:2]) < 0.02] *= 40.0
+    vis.flag = (rng.random(vis.flag.shape) < 0.1).astype(np.uint8)
+    if dtype == "c64":
+        vis = vis.copy(data=vis.data.astype(np.complex64), model=vis.model.astype(np.complex64),
+                       weight=vis.weight.astype(np.float32))
+        resid = resid.astype(np.complex64)
+    v = qc.device_vis(vis, DEV)
+    r = torch.as_tensor(resid).to(DEV)
+    t = qc.device_term(term, DEV)
+    odd = v.copy(weight=shifted(v.weight))
+    w, s2 = qc_lib.robust_weights(v, r, nu=2.5)
+    w_odd, s2_odd = qc_lib.robust_weights(odd, shifted(r), nu=2.5)
+    assert s2 == s2_odd and torch.equal(w, w_odd)
+    want, want_s2 = o_rob.robust_weights(vis, resid, 2.5)
+    tol = 1e-12 if dtype == "c128" else 1e-6
+    assert abs(s2 - want_s2) <= 1e-12 * want_s2
+    assert (np.abs(w.cpu().numpy() - want) <= tol * np.abs(want)).all()
+    w_in = v.weight.clone()
+    got, _ = qc_lib.robust_weights(v.copy(weight=w_in), r, nu=2.5, out=w_in)      # in place
+    assert torch.equal(got, w)
+    # s2 far outside the range of one division: the weights do not depend on a common scale
+    if dtype == "c128":
+        far, _ = qc_lib.robust_weights(v, r * 1e-70, nu=2.5)
+        assert (np.abs(far.cpu().numpy() - want) <= 1e-11 * np.abs(want)).all()
+    c = qc_lib.corrected_weights(v, [t])
+    assert torch.equal(c, qc_lib.corrected_weights(odd, [t]))
+    want = o_rob.corrected_weights(vis, [term])
+    assert (np.abs(c.cpu().numpy() - want) <= (1e-12 if dtype == "c128" else 2e-6) * np.abs(want)).all()
+    for mode in ("global", "baseline"):
+        f, n_new, _ = qc_lib.mad_flag(v, r, mode=mode, k=6.0)
+        f_odd, n_odd, _ = qc_lib.mad_flag(odd, shifted(r), mode=mode, k=6.0)
+        want, _ = o_flag.mad_flag(vis, resid, 6.0, mode)
+        assert np.array_equal(f.cpu().numpy(), want) and torch.equal(f, f_odd) and n_new == n_odd
