@@ -151,7 +151,8 @@ const char* qc_last_error(const qc_ctx* ctx);
 double      qc_last_kernel_ms(qc_ctx* ctx);
 
 /* Launch shape of the per-interval solve used by qc_solve_interval,
- * qc_solve_chain: waves per workgroup (1, 2, 4, 8; 0 = 4) and rows per
+ * qc_solve_chain: waves per workgroup (1, 2, 4, 8; 0 = chosen by the number
+ * and size of the intervals, 4 in the split schedule) and rows per
  * wavefront step (1, 2, 4; 0 = 4 rows of 16 lanes).
  * Multi-row steps apply to single-term, single-direction chains only.
  * rows_per_step 8 sets the split schedule of one-channel intervals (a

@@ -394,54 +394,126 @@ double qc_last_kernel_ms(qc_ctx* ctx) {
 
 }  // extern "C"
 
+// The work of one pass over the intervals of a solve, as the choices below see it.
+struct PassShape {
+  int n_int;
+  double n_samples, avg, rows;   // samples in all and per interval, rows per interval
+  int rps;                       // rows per wavefront step
+  double chunks;                 // steps per row
+  double step_us;                // one step of a lone workgroup of four wavefronts
+  int fit;                       // workgroups of four wavefronts that the chip holds
+  bool fp64, wide;               // wide: kernels held to four wavefronts
+  double stream_us;              // one read of the inputs
+
+  double steps(int waves) const { return std::ceil(rows / (waves * (double)rps)) * chunks; }
+  // Estimate of one fused pass in microseconds: the workgroups of a round take their
+  // steps one after the other or wait for the memory; the last round may leave
+  // the chip half empty.  Eight wavefronts on a compute unit take a fifth (FP64:
+  // two fifths) longer per step than four: full-Jones, 80 intervals of 1.3e5
+  // samples, MIXED 1.44 / 1.21 us, FP64 1.46 / 0.92 us.
+  double fused_us(int waves) const {
+    const int fit_w = std::max(1, fit * 4 / waves);
+    const double us = steps(waves) * step_us * (waves <= 4 ? 1.0 : fp64 ? 1.4 : 1.2);
+    const int full = n_int / fit_w, rest = n_int - full * fit_w;
+    return 12.0 + full * std::max(stream_us * fit_w / n_int, us) +
+           (rest ? std::max(stream_us * rest / n_int, us) : 0.0);
+  }
+};
+
+static PassShape pass_shape(const qc_ctx* ctx, const qc_vis* vis, const qc_term& ta, bool single, const SolveLaunch& L) {
+  PassShape S;
+  S.n_int = ta.n_gt * ta.n_gf;
+  S.n_samples = (double)vis->n_row * vis->n_chan;
+  S.rows = (double)vis->n_row / std::max(ta.n_gt, 1);
+  S.avg = S.n_samples / std::max(S.n_int, 1);
+  const int n_dir = single ? 1 : vis->n_dir;
+  const bool lane_rows = !single && L.max_int_chan <= 4 && ta.n_gdir == 1 && !L.left_general;
+  S.fp64 = !L.prec_mixed;
+  S.wide = !single && (L.left_general || (!L.diag_chain && S.fp64));
+  S.rps = single ? (L.rows_per_step > 0 ? L.rows_per_step : 4) : lane_rows ? 64 : 1;
+  S.chunks = lane_rows ? L.max_int_chan : std::ceil(L.max_int_chan / (64.0 / S.rps));
+  S.step_us = single ? 1.25 : lane_rows ? 10.0 : 1.25 * (1.0 + 0.75 * n_dir);
+  S.fit = ctx->n_cu * (S.fp64 ? 2 : single ? 4 : 3);
+  const double real = L.vis_is_c128 ? 8.0 : 4.0;
+  const double bytes = S.n_samples * (real * (8.0 + 8.0 * n_dir + vis->n_wcorr) + 1.0);
+  S.stream_us = bytes / (S.fp64 ? 4.2e6 : 6e6);                  // 6 TB/s, FP64 4.2 TB/s
+  return S;
+}
+
+// Wavefronts per workgroup of the fused schedule, where the caller has not chosen.
+//
+// Where the intervals leave the chip room, eight: an interval's pass is a chain of
+// steps, and twice the wavefronts halve it.  Measured (whole solves, four / eight):
+// 24 diagonal FP64 intervals of 840 samples 0.49 / 0.40 ms, 400 MIXED ones of 3040
+// 0.37 / 0.31 ms; 190 full-Jones FP64 ones of 1.2e5 5.2 / 3.9 ms; chains over four
+// directions, 64 intervals of 9920 samples 13.5 / 7.7 ms.  Room is one workgroup per
+// compute unit, two for the MIXED single-term kernels (400 FP64 ones of 3840
+// samples 0.48 / 0.52 ms; 640 MIXED ones of 1.3e5 8.6 / 9.5 ms).
+// Where many small intervals wait in line, fewer: each is mostly sums and block
+// solves, which a workgroup does at the pace of its barriers, so more intervals at once
+// are worth more than a shorter one.  25600 full-Jones MIXED intervals of 112
+// samples 5.5 ms with four, 3.7 with two, 3.0 with one; of 480 samples 9.1 / 7.4 / 6.9;
+// of 960 8.9 / 7.3 / 7.6 (diagonal FP64 10.5 / 9.3 / 9.1); 12800 of 3968 12.6 /
+// 12.5 / 13.4; 1600 of 960 0.58 / 0.55 / 0.80.  A wavefront alone takes up to 16
+// steps, two together up to 16 each.
+// Levenberg-Marquardt stays at four: its accepted steps hang on the last bits of
+// chi^2, which differ with the number of partial sums.
+static int fused_waves(const qc_ctx* ctx, const PassShape& S, bool single, bool lm) {
+  if (lm) return 4;
+  if (S.n_int <= ctx->n_cu * (single && !S.fp64 ? 2 : 1)) return S.wide ? 4 : 8;
+  if (single && S.n_int >= 8 * ctx->n_cu) {
+    if (S.steps(1) <= 16.0) return 1;
+    if (S.steps(2) <= 16.0) return 2;
+  }
+  return 4;
+}
+
 // Parts per interval of a solve (1: the fused schedule), by an estimate of
 // one pass of each schedule in microseconds.
 //
-// Fused: a workgroup of four wavefronts takes an interval of its own, so a pass
-// takes at least its steps one after the other; where n_int is no multiple of
-// the workgroups the chip holds, the last ones run with the chip half empty.
-// Split: the same work spread over the chip, plus the launches, the sums of the
-// parts and an update kernel.  Measured (MI355X, whole solves, fused against
-// split): 35 diagonal intervals of 1.6e5 samples 9.1 / 1.1 ms; 80 full-Jones
-// ones of 1.3e5 5.5 / 1.5 ms; 1100 of them 19.2 / 16.2 ms, 1600 22.0 / 22.0; 640
+// Fused: a workgroup takes an interval of its own (PassShape::fused_us).  Split: the
+// same work spread over the chip, plus the launches, the sums of the
+// parts and an update kernel.  Measured (MI355X, whole solves, fused with four
+// wavefronts against split): 35 diagonal intervals of 1.6e5 samples 9.1 / 1.1 ms (eight:
+// 5.1); 80 full-Jones ones of 1.3e5 5.5 / 1.5 ms (3.3); 190 FP64 ones of 1.2e5 5.2 /
+// 4.1 (3.9); 1100 of them 19.2 / 16.2 ms, 1600 22.0 / 22.0; 640
 // diagonal ones 8.6 / 8.9 ms; 400 of 3040 samples 0.37 / 0.49 ms; 4 of 19200
-// samples 1.13 / 0.35 ms; one delay interval of 5.7e5 samples x 3 directions
+// samples 1.13 / 0.35 ms (0.70); one delay interval of 5.7e5 samples x 3 directions
 // 201 / 1.1 ms.  Constants: a step of a lone workgroup takes 1.2-1.4 us in
 // the single-term kernels, 3.6-5.1 us in the chain kernels over 3-4
 // directions and 9-11 us with one row per lane; a pass with its update costs about
-// 12 us beyond its steps fused and 25 us split.  Levenberg-Marquardt keeps to large
-// intervals (2^18 samples on average): its accepted steps hang on the last bits
-// of chi^2, which differ between the schedules.
-static int split_parts(const qc_ctx* ctx, const qc_vis* vis, const qc_term& ta, bool single, const SolveLaunch& L,
-                       bool lm) {
-  const int n_int = ta.n_gt * ta.n_gf;
-  const double n_samples = (double)vis->n_row * vis->n_chan;
-  const double rows = (double)vis->n_row / std::max(ta.n_gt, 1);
-  const double avg = n_samples / n_int;
-  const int n_dir = single ? 1 : vis->n_dir;
-  const bool fp64 = !L.prec_mixed;
-  const bool lane_rows = !single && L.max_int_chan <= 4 && ta.n_gdir == 1 && !L.left_general;
-  const int rps = single ? 4 : lane_rows ? 64 : 1;
-  const double chunks = lane_rows ? L.max_int_chan : std::ceil(L.max_int_chan / (64.0 / rps));
-  const double steps = std::ceil(rows / (4.0 * rps)) * chunks;
-  const double step_us = single ? 1.25 : lane_rows ? 10.0 : 1.25 * (1.0 + 0.75 * n_dir);
-  const int fit = ctx->n_cu * (fp64 ? 2 : single ? 4 : 3);
-  const double real = L.vis_is_c128 ? 8.0 : 4.0;
-  const double pass_bytes = n_samples * (real * (8.0 + 8.0 * n_dir + vis->n_wcorr) + 1.0);
-  const double stream_us = pass_bytes / 6e6;                     // 6 TB/s
-  const bool large = n_int < 4 * ctx->n_cu && avg >= (double)(1 << 18);   // split whatever the estimate
+// 12 us beyond its steps fused and 25 us split; FP64 passes read 4.2 TB/s.
+// Levenberg-Marquardt keeps to large intervals (2^18 samples on average): its
+// accepted steps hang on the last bits of chi^2, which differ between the schedules.
+//
+// The parts of all intervals together fill whole rounds of the chip: a few
+// workgroups over a round run on an empty one.  80 full-Jones intervals take 1.82 ms in
+// 13 parts each (1040 workgroups of 1024 at once), 1.50 in 8; 190 FP64 ones 4.47 ms in
+// 6 (1140 of 512), 4.07 in 8 (1520).
+static int split_parts(const qc_ctx* ctx, const qc_vis* vis, const qc_term& ta, const PassShape& S, int waves, bool lm) {
+  const int n_int = S.n_int;
+  const bool large = n_int < 4 * ctx->n_cu && S.avg >= (double)(1 << 18);   // split whatever the estimate
   if (lm && !large) return 1;
   if (!large) {
-    const int full = n_int / fit, rest = n_int - full * fit;
-    const double fused_us = 12.0 + full * std::max(stream_us * fit / n_int, steps * step_us) +
-                            (rest ? std::max(stream_us * rest / n_int, steps * step_us) : 0.0);
-    const double split_us = 25.0 + std::max(stream_us, n_int * steps * step_us / fit);
-    if (fused_us <= 1.1 * split_us + 10.0) return 1;
+    const double split_us = 25.0 + std::max(S.stream_us, n_int * S.steps(4) * S.step_us / S.fit);
+    if (S.fused_us(S.wide ? std::min(waves, 4) : waves) <= 1.1 * split_us + 10.0) return 1;
   }
-  double wg = std::min((double)SPLIT_WG_PER_CU, std::max((double)SPLIT_WG_PER_CU_MIN,
-                                                         n_samples / SPLIT_PART_SAMPLES / ctx->n_cu));
-  const double most = std::max(2.0, std::min(rows / SPLIT_MIN_ROWS, avg / SPLIT_MIN_SAMPLES));
-  const int parts = (int)std::max(2.0, std::min(std::ceil(wg * ctx->n_cu / n_int), std::floor(most)));
+  const double wg = std::min((double)SPLIT_WG_PER_CU, std::max((double)SPLIT_WG_PER_CU_MIN,
+                                                               S.n_samples / SPLIT_PART_SAMPLES / ctx->n_cu));
+  const double most = std::max(2.0, std::min(S.rows / SPLIT_MIN_ROWS, S.avg / SPLIT_MIN_SAMPLES));
+  // the fewest parts from this number on that leave at most a sixteenth of their
+  // last round empty; else the fullest up to twice as many
+  const int least = (int)std::max(2.0, std::min(std::floor(wg * ctx->n_cu / n_int), std::floor(most)));
+  int parts = least;
+  double best = 0.0;
+  for (int p = least; p <= std::min(2 * least, (int)most) && best < 0.9375; ++p) {
+    const double rounds = (double)n_int * p / S.fit;
+    const double full = rounds / std::ceil(rounds);
+    if (full > best) {
+      best = full;
+      parts = p;
+    }
+  }
   // the partial sums (24 values per block at most) stay below 2 GiB
   const double blocks = (double)n_int * parts * vis->n_ant * (ta.n_gdir == 1 ? 1 : 4);
   return blocks * 24.0 * sizeof(double) > 2147483648.0 ? 1 : parts;
@@ -547,7 +619,8 @@ static qc_status solve_interval_impl(qc_ctx* ctx, const qc_vis* vis, qc_term* ch
   L.max_iter = opts->max_iter;
   L.damping = resolve_damping(opts->damping, ta);
   L.err = ctx->d_err;
-  L.waves = ctx->waves;
+  L.waves = ctx->waves ? ctx->waves : 4;
+  L.waves_auto = 0;
   L.max_int_chan = ctx->max_int_chan;
   L.dir_ident = ta.n_gdir > 1 && ta.n_gdir == vis->n_dir && ta.n_gdir <= 4;
   for (int d = 0; L.dir_ident && d < vis->n_dir; ++d)
@@ -573,12 +646,14 @@ static qc_status solve_interval_impl(qc_ctx* ctx, const qc_vis* vis, qc_term* ch
   if (fold) fold = spare_memory(ctx, ctx->d_fold, ctx->fold_cap, chain_fold_bytes(L));
   if (lm && ta.type == QC_TERM_DELAY_OFFSET)
     return fail(ctx, QC_E_UNSUPPORTED, "Levenberg-Marquardt takes no delay-and-offset term");
+  const PassShape shape = pass_shape(ctx, vis, ta, single_chain || fold, L);
+  const int waves = ctx->waves ? ctx->waves : fused_waves(ctx, shape, single_chain || fold, lm);
   if (fixed) {
     parts = 1;                                 // the split schedule's state is context memory
   } else if (ctx->split_parts > 1) {
     parts = ctx->split_parts;
   } else if (ctx->split_parts == 0 && !opts->chisq_ref && n_int > 0) {
-    parts = split_parts(ctx, vis, ta, single_chain || fold, L, lm);
+    parts = split_parts(ctx, vis, ta, shape, waves, lm);
   }
   if (parts > 1 && opts->chisq_ref)
     return fail(ctx, QC_E_UNSUPPORTED, "the split schedule does not take chisq_ref");
@@ -715,6 +790,8 @@ static qc_status solve_interval_impl(qc_ctx* ctx, const qc_vis* vis, qc_term* ch
   if (e != hipSuccess) {
     // reported below
   } else if (parts <= 1) {
+    L.waves = waves;
+    L.waves_auto = ctx->waves == 0;
     e = launch_solve(L, nullptr, s, &lds);
   } else {
     P.phase = 0;
@@ -787,7 +864,7 @@ qc_status qc_ctx_set_tile(qc_ctx* ctx, int32_t waves, int32_t rows_per_step) {
     return fail(ctx, QC_E_ARG, "waves must be 1, 2, 4 or 8 (0 = default)");
   if (rows_per_step != 0 && rows_per_step != 1 && rows_per_step != 2 && rows_per_step != 4 && rows_per_step != 8)
     return fail(ctx, QC_E_ARG, "rows_per_step must be 1, 2, 4 or 8 (0 = from the interval width)");
-  ctx->waves = waves ? waves : 4;
+  ctx->waves = waves;
   ctx->rows_per_step = rows_per_step;
   return QC_OK;
 }

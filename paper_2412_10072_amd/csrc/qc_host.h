@@ -56,7 +56,7 @@ struct qc_ctx {
   size_t dh_cap = 0;
   hipEvent_t ev0 = nullptr, ev1 = nullptr;
   bool timed = false;
-  int waves = 4;              // waves per workgroup of the per-interval solve
+  int waves = 0;              // waves per workgroup of the per-interval solve (0: by the intervals)
   int rows_per_step = 0;      // 0: the kernel default
   int split_parts = 0;        // 0: automatic, 1: never split, > 1: parts per interval
   int n_cu = 0;               // compute units of the device

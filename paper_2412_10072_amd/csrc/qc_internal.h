@@ -390,6 +390,7 @@ struct SolveLaunch {
   int damping;                // resolved: 0 full, 1 half, 2 alternate
   int* err;
   int waves;                  // waves per workgroup
+  int waves_auto;             // chosen by the library: eight only where their LDS fits
   int max_int_chan;           // channels of the widest interval
   int rows_per_step;          // 0: the kernel default
   const double* chisq_ref;    // may be null

@@ -261,13 +261,18 @@ hipError_t launch_split_update(K ku, const SolveLaunch& L, const SplitLaunch& P,
   return hipGetLastError();
 }
 
-// Waves per workgroup: the context's choice; at most 4 for the kernels of
+// Waves per workgroup: the context's choice, or the library's, of which eight fall
+// back to four where their LDS slots do not fit; at most 4 for the kernels of
 // wide per-lane state (their launch bound), and for the full-block kernels
 // halved while their per-wave LDS slots (24 values per antenna and gain
 // direction for a full-Jones term) do not fit.
 template <int KIND, typename T, int NG, int CHM>
-int fit_waves(int n_ant, int nw, bool lane_rows) {
+int fit_waves(const SolveLaunch& L, bool lane_rows) {
+  const int n_ant = L.vis.n_ant;
+  int nw = L.waves;
   if constexpr (wide_state<CHM, T>()) nw = std::min(nw, 4);
+  if (L.waves_auto && nw > 4 && interval_lds_bytes<KIND, T, NG, CHM == CHAIN_LEFT>(n_ant, nw, lane_rows) > 160 * 1024)
+    nw = 4;
   if constexpr (CHM == CHAIN_LEFT) {
     while (nw > 1 && interval_lds_bytes<KIND, T, NG, true>(n_ant, nw, lane_rows) > 160 * 1024) nw /= 2;
   }
@@ -277,7 +282,7 @@ int fit_waves(int n_ant, int nw, bool lane_rows) {
 template <int KIND, typename S, typename T, int CHM, int NG, int RPS, bool SKY = false>
 hipError_t launch_split_one(const SolveLaunch& L, const SplitLaunch& P, hipStream_t stream, size_t* lds_out) {
   constexpr bool FB = CHM == CHAIN_LEFT;
-  const int nw = fit_waves<KIND, T, NG, CHM>(L.vis.n_ant, L.waves, RPS == 64);
+  const int nw = fit_waves<KIND, T, NG, CHM>(L, RPS == 64);
   const size_t lds = interval_lds_bytes<KIND, T, NG, FB>(L.vis.n_ant, nw, RPS == 64);
   const size_t lds_u = interval_lds_bytes<KIND, T, NG, FB>(L.vis.n_ant, 0);
   if (lds_out) *lds_out = lds;
@@ -359,7 +364,7 @@ hipError_t launch_band(const SolveLaunch& L, const SplitLaunch& P, hipStream_t s
 template <int KIND, typename S, typename T, int CHM, int NG, int RPS, bool LMT = false, bool SKY = false>
 hipError_t launch_one(const SolveLaunch& L, hipStream_t stream, size_t* lds_out) {
   constexpr bool FB = CHM == CHAIN_LEFT;
-  const int nw = fit_waves<KIND, T, NG, CHM>(L.vis.n_ant, L.waves, RPS == 64);
+  const int nw = fit_waves<KIND, T, NG, CHM>(L, RPS == 64);
   const size_t lds = interval_lds_bytes<KIND, T, NG, FB>(L.vis.n_ant, nw, RPS == 64);
   if (lds_out) *lds_out = lds;
   if (lds > 160 * 1024) return hipErrorInvalidValue;
