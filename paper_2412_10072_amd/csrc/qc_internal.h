@@ -294,6 +294,7 @@ struct PComp {
 struct SkyArgs {
   const PComp* comp;       // direction order
   const int* off;          // [n_dir + 1] first component of each direction
+  int n_comp;
   const double* uvw;       // [n_row][3] baseline coordinates (m)
   int spectral;            // any spectral index nonzero
   int polarised;           // any component with Q, U or V
