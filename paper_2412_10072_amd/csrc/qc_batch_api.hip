@@ -40,8 +40,11 @@ constexpr double EST_BYTES_PER_US = 6e6;
 constexpr double EST_STEP_US = 1.3;
 constexpr double TEAM_MIN_STEPS = 48.0;
 // An interval is a team's where one workgroup would take longer for it than
-// this share of the whole batch streamed at full rate.
-constexpr double TEAM_SHARE = 0.25;
+// this share of the whole batch streamed at full rate: early enough that none is
+// left running alone at the end.  24 problems MIXED 14.3 ms at 0.25, 13.4 at
+// 0.1, 12.8 at 0.03 and 0.01 (FP64 16.1, 15.4, 15.5, 15.4); 24 of a tenth of
+// the samples 3.85, 3.76, 3.60, 3.68.
+constexpr double TEAM_SHARE = 0.03;
 
 }  // namespace
 
