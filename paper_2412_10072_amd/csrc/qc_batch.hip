@@ -11,9 +11,10 @@
 // queue is empty, so every workgroup reaches the exit.  The bucket kernels
 // run on parallel branches of one graph.
 //
-// Schedule: each bucket has (waves per workgroup, rows per step).  Defaults
-// come from the channel width; qc_batch_tune times every candidate on the
-// batch itself and keeps the fastest per bucket.
+// Schedule: each bucket has (waves per workgroup, rows per step), by default 8
+// (4 for a bucket of many intervals) and 4; qc_batch_tune times every candidate
+// on the batch itself and keeps the fastest per bucket.  Intervals much larger
+// than the rest go to teams of workgroups instead (k_batch_team).
 
 #include <algorithm>
 #include <cstring>
