@@ -1301,11 +1301,11 @@ __device__ __forceinline__ void solve_interval(const Job& J) {
   constexpr int NVP = pow2ceil(FB_PER_G ? NV : NVG);
   constexpr int LPR = 64 / RPS;              // lanes per row
   constexpr bool LANE_ROWS = (LPR == 1);     // one row per lane: flush by lane_flush
-  // keep antenna-p sums in registers over a p-run; with several gain directions
-  // where the kernel unrolls them and the registers hold them (MIXED, 198 VGPRs):
-  // a row is then reduced once, not twice (four directions, 64 antennas, 60 times
-  // x 256 channels: 26.6 -> 25.1 ms a solve)
-  constexpr bool PACC = (NG == 1 || (DIR_ID && sizeof(T) == 4)) && !LANE_ROWS;
+  // Keep antenna-p sums in registers over a p-run.  (Not with several gain
+  // directions: their rows are summed into the compensated slots one by one, and
+  // an FP32 sum over a run of any length would be short of that.  Four directions,
+  // 64 antennas, 60 times x 256 channels: 26.6 ms a solve, 25.1 kept in registers.)
+  constexpr bool PACC = (NG == 1) && !LANE_ROWS;
   // FP64 single-term passes over complex64 data with full-Jones or
   // real-parameter terms: the loads of the next chunk (and the row indices of
   // the next step) are issued before the current chunk is computed.  These
