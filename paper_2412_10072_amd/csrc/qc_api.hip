@@ -660,7 +660,7 @@ static qc_status solve_interval_impl(qc_ctx* ctx, const qc_vis* vis, qc_term* ch
   // intervals of one channel each, in channel order, on a diagonal chain with
   // one gain direction: the split pass over 16 channels per wavefront
   bool band = parts > 1 && !sky && L.diag_chain && !L.left_general && one_chan && ta.n_gdir == 1 &&
-              vis->n_row < (1LL << 31) && band_lds_bytes_for(vis->n_ant, L.prec_mixed != 0, 8) <= 64 * 1024;
+              vis->n_row < (1LL << 31) && band_lds_bytes_for(vis->n_ant, 8) <= (L.prec_mixed ? 160 : 64) * 1024;
   // diagonal chains: the direction-dependent fixed terms, when all are
   // diagonal gains and at most BAND_MAX_DD, tabulated once per solve for every
   // pass (the band pass takes no other kind).  A pointing term differs by
@@ -675,14 +675,18 @@ static qc_status solve_interval_impl(qc_ctx* ctx, const qc_vis* vis, qc_term* ch
   }
   if (!L.dd_tabled) L.n_dd = 0;
   if (!L.dd_tabled && !fold) band = false;
-  // 4 rows x 16 channels per step (measured faster than 8 x 8 on the 64-antenna
-  // bandpass: 11.1 against 12.9 ms per pass), unless asked otherwise or its LDS
-  // slots do not fit
-  L.band_rows = (ctx->rows_per_step == 8 || band_lds_bytes_for(vis->n_ant, L.prec_mixed != 0, 4) > 64 * 1024) ? 8 : 4;
+  // 4 rows x 16 channels per step, or as asked; 8 x 8, whose LDS slots are half as
+  // large, where those do not fit and, in MIXED, where they leave a compute unit
+  // fewer than six wavefronts (solves of 10 updates, 4 x 16 / 8 x 8: 28 antennas, 100
+  // times x 256 channels 2.40 / 2.57 ms; 64, 100 x 512 26.0 / 19.2; four directions
+  // folded, 60 x 256 9.6 / 7.3; FP32 slots took 17.1 and 6.8 in 4 x 16)
+  const size_t rows4 = band_lds_bytes_for(vis->n_ant, 4);
+  L.band_rows = (ctx->rows_per_step == 8 || rows4 > 64 * 1024 ||
+                 (L.prec_mixed && ctx->rows_per_step != 4 && rows4 > 160 * 1024 / 6)) ? 8 : 4;
   if (band && ctx->split_parts == 0) {
     const long long units = (long long)((vis->n_chan + 64 / L.band_rows - 1) / (64 / L.band_rows)) * ta.n_gt;
     const double rows_per_int = (double)vis->n_row / std::max(ta.n_gt, 1);
-    const int fit = (int)(160 * 1024 / band_lds_bytes_for(vis->n_ant, L.prec_mixed != 0, L.band_rows));
+    const int fit = (int)(160 * 1024 / band_lds_bytes_for(vis->n_ant, L.band_rows));
     parts = (int)((long long)std::max(1, std::min(BAND_WAVES_PER_CU, fit)) * ctx->n_cu / units);
     parts = std::max(2, std::min(parts, (int)std::max(1.0, rows_per_int / 32.0)));
   }

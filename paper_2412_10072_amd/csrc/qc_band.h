@@ -21,8 +21,12 @@
 // collision (distinct q per row, distinct channel per lane), so they are added in
 // program order and the result does not depend on timing.  At
 // each change of time the LDS slots are added into the part's FP64 partial
-// blocks (in the layout the split update sums), so an FP32 slot holds at most
-// one time's sums (<= n_ant - 1 rows per antenna).
+// blocks (in the layout the split update sums).
+//
+// The sums are FP64 in MIXED too (contributions FP32): nothing bounds the rows of
+// one time and antenna (a baseline may repeat), and plain FP32 slots over 8000 equal
+// rows were off by 1e-4 of the update, where the other MIXED passes compensate
+// theirs.
 #pragma once
 
 #include "qc_interval.h"
@@ -94,6 +98,22 @@ __device__ __forceinline__ void band_add_turns(bool add, int g, int ant, int cl,
   }
 }
 
+// acc += the contribution of one sample, formed in T.
+template <typename T>
+__device__ __forceinline__ void band_contrib(const m22<T>& B, const m22<T>& WR, T w0, T w1, T w2, T w3, cx<T> g0, cx<T> g1,
+                                             double* acc) {
+  if constexpr (sizeof(T) == 8) {
+    contrib<KIND_DIAG, true, T>(cone<T>(), cone<T>(), B, WR, w0, w1, w2, w3, g0, g1, T(1), acc);
+  } else {
+    T v[BAND_NV];
+#pragma unroll
+    for (int k = 0; k < BAND_NV; ++k) v[k] = T(0);
+    contrib<KIND_DIAG, true, T>(cone<T>(), cone<T>(), B, WR, w0, w1, w2, w3, g0, g1, T(1), v);
+#pragma unroll
+    for (int k = 0; k < BAND_NV; ++k) acc[k] += (double)v[k];
+  }
+}
+
 // x of the lane 8 apart in the same 16-lane row (DPP row rotate by 8)
 constexpr int DPP_ROW_ROR8 = 0x128;
 __device__ __forceinline__ float ror8(float x) {
@@ -139,7 +159,7 @@ __device__ __forceinline__ int ld_uniform(const int* base, long long i) {
 // ND: direction-dependent fixed terms, read from their tables (L.dd_tab).
 template <typename S, typename T, int ND, int CW>
 __global__ void __launch_bounds__(64) k_band_pass(SolveLaunch L, int n_part, double* partials, const uint8_t* done) {
-  using A = T;
+  using A = double;                     // the sums
   constexpr int NV = BAND_NV;
   constexpr int NR = 64 / CW;           // rows per step
   const VisArgs& V = L.vis;
@@ -192,7 +212,7 @@ __global__ void __launch_bounds__(64) k_band_pass(SolveLaunch L, int n_part, dou
   }
 
   bool first = true;          // no FP64 flush yet: the first one stores
-  A chi = A(0);
+  T chi = T(0);
   double chi64 = 0.0;
   A pacc[8];
 #pragma unroll
@@ -232,7 +252,7 @@ __global__ void __launch_bounds__(64) k_band_pass(SolveLaunch L, int n_part, dou
     }
     __syncthreads();
     chi64 += (double)chi;
-    chi = A(0);
+    chi = T(0);
     first = false;
   };
 
@@ -349,8 +369,8 @@ __global__ void __launch_bounds__(64) k_band_pass(SolveLaunch L, int n_part, dou
     A qv[NV];
 #pragma unroll
     for (int k = 0; k < NV; ++k) qv[k] = A(0);
-    contrib<KIND_DIAG, true, T>(cone<T>(), cone<T>(), B, WR, w0, w1, w2, w3, hp0, hp1, T(1), pacc);
-    contrib<KIND_DIAG, true, T>(cone<T>(), cone<T>(), Bc, herm(WR), w0, w2, w1, w3, hq0, hq1, T(1), qv);
+    band_contrib<T>(B, WR, w0, w1, w2, w3, hp0, hp1, pacc);
+    band_contrib<T>(Bc, herm(WR), w0, w2, w1, w3, hq0, hq1, qv);
     chi = chisq_acc(WR, R, chi);
 
     const bool add = row_ok && cin;
@@ -418,7 +438,7 @@ struct BandGain {
 
 template <typename S, typename T, int CW>
 __global__ void __launch_bounds__(64) k_band_single(SolveLaunch L, int n_part, double* partials, const uint8_t* done) {
-  using A = T;
+  using A = double;                     // the sums
   constexpr int NV = BAND_NV;
   constexpr int NR = 64 / CW;           // rows per step
   const VisArgs& V = L.vis;
@@ -454,7 +474,7 @@ __global__ void __launch_bounds__(64) k_band_single(SolveLaunch L, int n_part, d
   const S* Wp = reinterpret_cast<const S*>(V.weight);
 
   bool first = true;          // no FP64 flush yet: the first one stores
-  A chi = A(0);
+  T chi = T(0);
   double chi64 = 0.0;
   A pacc[NV];
 #pragma unroll
@@ -497,7 +517,7 @@ __global__ void __launch_bounds__(64) k_band_single(SolveLaunch L, int n_part, d
     }
     __syncthreads();
     chi64 += (double)chi;
-    chi = A(0);
+    chi = T(0);
     first = false;
   };
 
@@ -569,8 +589,8 @@ __global__ void __launch_bounds__(64) k_band_single(SolveLaunch L, int n_part, d
     A qv[NV];
 #pragma unroll
     for (int k = 0; k < NV; ++k) qv[k] = A(0);
-    contrib<KIND_DIAG, true, T>(cone<T>(), cone<T>(), B, WR, w0, w1, w2, w3, h0.p0, h0.p1, T(1), pacc);
-    contrib<KIND_DIAG, true, T>(cone<T>(), cone<T>(), Bc, herm(WR), w0, w2, w1, w3, h0.q0, h0.q1, T(1), qv);
+    band_contrib<T>(B, WR, w0, w1, w2, w3, h0.p0, h0.p1, pacc);
+    band_contrib<T>(Bc, herm(WR), w0, w2, w1, w3, h0.q0, h0.q1, qv);
     chi = chisq_acc(WR, R, chi);
 
     // two rows of the step that share antenna q are added one after the other
@@ -608,6 +628,11 @@ hipError_t launch_band_single(const SolveLaunch& L, int n_part, double* partials
   const TermArgs& ta = L.chain.t[L.chain.active];
   const int n_slices = (L.vis.n_chan + CW - 1) / CW;
   const size_t n = (size_t)ta.n_gt * n_slices * L.vis.n_ant * 2 * CW;
+  if (lds > 64 * 1024) {
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_band_single<S, T, CW>),
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return e;
+  }
   hipLaunchKernelGGL((k_band_gains<T, CW>), dim3((unsigned)((n + 255) / 256)), dim3(256), 0, stream,
                      (const double2*)L.gains, ta.n_gf, L.vis.n_ant, n_slices, n, reinterpret_cast<cx<T>*>(L.band_gains));
   hipLaunchKernelGGL((k_band_single<S, T, CW>), dim3(grid), dim3(64), lds, stream, L, n_part, partials, done);

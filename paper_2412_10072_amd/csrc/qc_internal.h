@@ -426,9 +426,9 @@ struct SolveLaunch {
 // Fills the steps (of `rows` rows at most) of the single-channel-interval
 // split pass for n_part parts per gain time (L.row_lo / row_hi) on `stream`.
 hipError_t launch_band_steps(const SolveLaunch& L, int n_part, int rows, BandStep* steps, hipStream_t stream);
-// LDS bytes of that pass for n_ant antennas (FP32 or FP64 sums) and `rows`
-// rows per step (64 / rows channels per wavefront)
-size_t band_lds_bytes_for(int n_ant, bool fp32, int rows);
+// LDS bytes of that pass for n_ant antennas and `rows` rows per step (64 / rows
+// channels per wavefront)
+size_t band_lds_bytes_for(int n_ant, int rows);
 // bytes of that pass's gain table (the active term alone over one direction)
 size_t band_gains_bytes(const SolveLaunch& L);
 // Table of direction-dependent fixed term j (diagonal gains) for that pass:

@@ -301,8 +301,8 @@ hipError_t launch_dd_table(const SolveLaunch& L, int j, void* table, hipStream_t
   return hipGetLastError();
 }
 
-size_t band_lds_bytes_for(int n_ant, bool fp32, int rows) {
-  return (fp32 ? sizeof(float) : sizeof(double)) * (size_t)n_ant * KindInfo<KIND_DIAG>::NV * (64 / rows);
+size_t band_lds_bytes_for(int n_ant, int rows) {
+  return sizeof(double) * (size_t)n_ant * KindInfo<KIND_DIAG>::NV * (64 / rows);
 }
 
 size_t band_gains_bytes(const SolveLaunch& L) {

@@ -322,10 +322,10 @@ hipError_t launch_split_one(const SolveLaunch& L, const SplitLaunch& P, hipStrea
 // pass, then the same update as for the other split passes.
 template <typename S, typename T>
 hipError_t launch_band(const SolveLaunch& L, const SplitLaunch& P, hipStream_t stream, size_t* lds_out) {
-  const size_t lds = band_lds_bytes_for(L.vis.n_ant, sizeof(T) == 4, L.band_rows);
+  const size_t lds = band_lds_bytes_for(L.vis.n_ant, L.band_rows);
   const size_t lds_u = interval_lds_bytes<KIND_DIAG, T, 1, false>(L.vis.n_ant, 0);
   if (lds_out) *lds_out = lds;
-  if (lds > 64 * 1024) return hipErrorInvalidValue;
+  if (lds > 160 * 1024) return hipErrorInvalidValue;
   auto ku = k_split_update<KIND_DIAG, T, 1, false>;
   if (lds_u > 64 * 1024) {
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(ku),
@@ -354,6 +354,11 @@ hipError_t launch_band(const SolveLaunch& L, const SplitLaunch& P, hipStream_t s
       kern = L.n_dd == 0 ? k_band_pass<S, T, 0, 8> : L.n_dd == 1 ? k_band_pass<S, T, 1, 8> : k_band_pass<S, T, 2, 8>;
     } else {
       kern = L.n_dd == 0 ? k_band_pass<S, T, 0, 16> : L.n_dd == 1 ? k_band_pass<S, T, 1, 16> : k_band_pass<S, T, 2, 16>;
+    }
+    if (lds > 64 * 1024) {
+      const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
+                                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+      if (e != hipSuccess) return e;
     }
     hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(64), lds, stream, L, P.n_part, P.partials, done);
     return launch_split_update(ku, L, P, (size_t)L.vis.n_ant * BAND_NV + 1, lds_u, stream);

@@ -72,3 +72,21 @@ def test_directional_solve_over_a_long_run(ctx):
     ctx.set_split(1)
     ctx.set_tile(1, 0)
     check(ctx, vis, [dE], 0, 1)
+
+
+@pytest.mark.parametrize("rows", [4, 8])
+@pytest.mark.parametrize("route", ["single", "chain", "folded chain"])
+def test_one_channel_intervals_over_a_long_run(ctx, route, rows):
+    """One-channel intervals whose one time repeats a baseline 8000 times, in two
+    parts (the pass over 16 or 8 channels per wavefront): a single term, a chain of
+    too few updates for the folded model, and one folded."""
+    say(f"one-channel MIXED sums, 8000 rows of one time, {route}, {rows} rows per step")
+    n_dir = 1 if route == "single" else 2
+    vis = constant_vis(1, 8000, 10, n_dir)
+    rng = np.random.default_rng(9)
+    chain = [unit_like(make_term(rng, "diag", 1, 10, 2, f_int=1, n_dir=n_dir))]
+    if route != "single":
+        chain.append(unit_like(make_term(rng, "diag", 1, 10, 2, n_dir=n_dir)))
+    ctx.set_split(2)
+    ctx.set_tile(0, rows)
+    check(ctx, vis, chain, 0, 3 if route == "folded chain" else 1)
