@@ -340,6 +340,8 @@ qc_status qc_ctx_destroy(qc_ctx* ctx) {
   hipFree(ctx->d_dh);
   hipFree(ctx->d_partials);
   hipFree(ctx->d_otab);
+  hipFree(ctx->d_outtab);
+  if (ctx->outtab_use.ev) hipEventDestroy(ctx->outtab_use.ev);
   hipFree(ctx->d_fold);
   hipFree(ctx->d_fl_stat);
   hipFree(ctx->d_fl_groups);
@@ -1148,15 +1150,17 @@ static qc_status outputs_common(qc_ctx* ctx, const qc_vis* vis, const qc_term* c
   void* table = nullptr;
   if (!sky && out_table_pays(L, vis, chain, n_term, maps)) {
     const size_t bytes = out_table_bytes(L);
-    if (grow(ctx->d_otab, ctx->otab_cap, bytes) == hipSuccess) table = ctx->d_otab;
+    if (grow(ctx->d_outtab, ctx->outtab_cap, bytes) == hipSuccess) table = ctx->d_outtab;
     else (void)hipGetLastError();              // no memory for it: the chain is formed per sample
   }
   HIP_TRY(ctx, hipEventRecord(ctx->ev0, s));
   if (table) {
+    HIP_TRY(ctx, scratch_take(ctx->outtab_use, s));
     HIP_TRY(ctx, launch_out_table(L, table, s));
     L.tab = table;
   }
   HIP_TRY(ctx, launch_outputs(L, s));
+  if (table) HIP_TRY(ctx, scratch_leave(ctx->outtab_use, s));
   HIP_TRY(ctx, hipEventRecord(ctx->ev1, s));
   ctx->timed = true;
   return QC_OK;

@@ -33,6 +33,13 @@ constexpr double SPLIT_MIN_ROWS = 16.0;
 // CU 51.8 ms a solve, 4 61.7, 8 71.8, 12 54.2, 24 64.1.
 constexpr int BAND_WAVES_PER_CU = 8;
 
+// Context scratch that a call's kernels may still read after the call returned.  A
+// call on another stream that writes it waits for them on the device.
+struct ScratchUse {
+  hipEvent_t ev = nullptr;             // after the last reader
+  hipStream_t stream = nullptr;
+};
+
 struct qc_ctx {
   int device = 0;
   std::string msg;
@@ -64,6 +71,9 @@ struct qc_ctx {
   size_t partials_cap = 0;
   unsigned char* d_otab = nullptr;    // fixed chain factors of diagonal chains
   size_t otab_cap = 0;
+  unsigned char* d_outtab = nullptr;  // the outputs' table of the direction-independent chain
+  size_t outtab_cap = 0;
+  ScratchUse outtab_use;
   unsigned char* d_fold = nullptr;    // folded model of a diagonal chain's solve
   size_t fold_cap = 0;
   // MAD flagging scratch
@@ -157,6 +167,21 @@ hipError_t grow(P*& ptr, size_t& cap, size_t n) {
   return hipSuccess;
 }
 
+// Before `s` writes that scratch, and after its last reader was put on `s`.
+inline hipError_t scratch_take(const ScratchUse& u, hipStream_t s) {
+  return u.ev && u.stream != s ? hipStreamWaitEvent(s, u.ev, 0) : hipSuccess;
+}
+inline hipError_t scratch_leave(ScratchUse& u, hipStream_t s) {
+  if (!u.ev) {
+    const hipError_t e = hipEventCreateWithFlags(&u.ev, hipEventDisableTiming);
+    if (e != hipSuccess) {
+      u.ev = nullptr;
+      return e;
+    }
+  }
+  u.stream = s;
+  return hipEventRecord(u.ev, s);
+}
 
 struct HostMaps {
   std::vector<int> t_map, f_map, d_map;

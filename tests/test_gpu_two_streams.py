@@ -1,0 +1,66 @@
+"""Calls on two streams of one context whose kernels overlap: each gives bit for
+bit what it gives alone, though both use the context's scratch memory (the outputs'
+chain table)."""
+import sys
+
+import pytest
+import torch
+
+from synth.problem import Term, Vis
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+def say(msg):
+    print(msg, flush=True)
+    sys.stdout.flush()
+
+
+def device_problem(seed, n_ant, n_time, n_chan, t_int, f_int, dtype=torch.complex64):
+    """Random data and model of one direction and a diagonal term near unit gains,
+    made on the device."""
+    g = torch.Generator(device=DEV).manual_seed(seed)
+    real = torch.float32 if dtype == torch.complex64 else torch.float64
+    p, q = torch.triu_indices(n_ant, n_ant, offset=1)
+    n = p.numel() * n_time
+
+    def cnormal(*shape, dt=real):
+        return torch.view_as_complex(torch.randn(*shape, 2, generator=g, device=DEV, dtype=dt))
+    i32 = dict(dtype=torch.int32, device=DEV)
+    vis = Vis(data=cnormal(n, n_chan, 4), model=cnormal(n, n_chan, 1, 4),
+              weight=torch.rand(n, n_chan, 4, generator=g, device=DEV, dtype=real) + 0.5,
+              flag=torch.zeros(n, n_chan, dtype=torch.uint8, device=DEV), ant1=p.repeat(n_time).to(**i32),
+              ant2=q.repeat(n_time).to(**i32), row_time=torch.arange(n_time).repeat_interleave(p.numel()).to(**i32),
+              chan_freq=1.0e9 + 1.0e6 * torch.arange(n_chan, dtype=torch.float64, device=DEV), n_ant=n_ant, n_time=n_time)
+    t_map = (torch.arange(n_time) // t_int).to(**i32)
+    f_map = (torch.arange(n_chan) // f_int).to(**i32)
+    shape = (int(t_map.max()) + 1, int(f_map.max()) + 1, n_ant, 1)
+    gains = torch.zeros(*shape, 4, dtype=torch.complex128, device=DEV)
+    gains[..., 0] = 1 + 0.2 * cnormal(*shape, dt=torch.float64)
+    gains[..., 3] = 1 + 0.2 * cnormal(*shape, dt=torch.float64)
+    term = Term(kind="diag", t_map=t_map, f_map=f_map, d_map=torch.zeros(1, **i32), n_gt=shape[0], n_gf=shape[1],
+                n_gdir=1, gains=gains, params=None, gain_flags=torch.zeros(shape, dtype=torch.int8, device=DEV),
+                direction_dependent=False, name="G")
+    return vis, term
+
+
+def test_outputs_with_tables_on_two_streams(qc_lib):
+    """Residuals through one solution per channel (tabulated) of two problems."""
+    say("tabulated residuals on two streams")
+    probs = [device_problem(11 + i, 40, 20, 512 - 64 * i, 1, 1) for i in range(2)]
+    alone = []
+    for vis, term in probs:
+        alone.append(qc_lib.residual(vis, [term]))
+        torch.cuda.synchronize()
+    streams = [torch.cuda.Stream() for _ in probs]
+    outs = [torch.empty_like(a) for a in alone]
+    torch.cuda.synchronize()
+    for _ in range(5):
+        for (vis, term), s, out in zip(probs, streams, outs):
+            qc_lib.residual(vis, [term], out=out, stream=s)
+        torch.cuda.synchronize()
+        for a, out in zip(alone, outs):
+            assert torch.equal(a, out)
+            out.zero_()
+        torch.cuda.synchronize()
