@@ -13,6 +13,7 @@
 
 #include "qc_host.h"
 #include "qc_hostcheck.h"
+#include "qc_schedule.h"
 
 using namespace qc;
 
@@ -521,9 +522,8 @@ static int split_parts(const qc_ctx* ctx, const qc_vis* vis, const qc_term& ta, 
   return blocks * 24.0 * sizeof(double) > 2147483648.0 ? 1 : parts;
 }
 
-// Memory of the context that a solve can do without: at most a sixteenth of the device's,
-// and, when it has to grow, an eighth of what is free (the arrays the caller
-// may still want come first); false: the solve goes without.
+// Memory of the context that a call can do without (spare_fits); false: the call goes
+// without.
 static bool spare_memory(qc_ctx* ctx, unsigned char*& ptr, size_t& cap, size_t bytes) {
   if (bytes == 0) return false;
   if (ptr && bytes <= cap) return true;
@@ -532,7 +532,7 @@ static bool spare_memory(qc_ctx* ctx, unsigned char*& ptr, size_t& cap, size_t b
     (void)hipGetLastError();
     return false;
   }
-  if (bytes > total_b / 16 || bytes > free_b / 8) return false;
+  if (!spare_fits(bytes, free_b, total_b)) return false;
   if (grow(ptr, cap, bytes) == hipSuccess) return true;
   (void)hipGetLastError();
   return false;
@@ -1149,9 +1149,8 @@ static qc_status outputs_common(qc_ctx* ctx, const qc_vis* vis, const qc_term* c
   L.tab = nullptr;
   void* table = nullptr;
   if (!sky && out_table_pays(L, vis, chain, n_term, maps)) {
-    const size_t bytes = out_table_bytes(L);
-    if (grow(ctx->d_outtab, ctx->outtab_cap, bytes) == hipSuccess) table = ctx->d_outtab;
-    else (void)hipGetLastError();              // no memory for it: the chain is formed per sample
+    // (without memory for it the chain is formed per sample)
+    if (spare_memory(ctx, ctx->d_outtab, ctx->outtab_cap, out_table_bytes(L))) table = ctx->d_outtab;
   }
   HIP_TRY(ctx, hipEventRecord(ctx->ev0, s));
   if (table) {
