@@ -157,6 +157,7 @@ qc_status validate_rows(qc_ctx* ctx, const qc_vis* v, hipStream_t s) {
   ChainArgs ca;
   fill_args(v, nullptr, 0, -1, va, ca);
   HIP_TRY(ctx, grow(ctx->d_rowpos, ctx->rowpos_cap, (size_t)v->n_time + 1));
+  HIP_TRY(ctx, solve_take(ctx, s, false));
   hipLaunchKernelGGL(k_clear, dim3(1), dim3(64), 0, s, ctx->d_err);
   if (v->n_row > 0) {
     const long long nb = (v->n_row + 255) / 256;
@@ -189,6 +190,7 @@ qc_status prepare(qc_ctx* ctx, const qc_vis* v, const qc_term* chain, int n_term
     HIP_TRY(ctx, grow(ctx->d_rowpos, ctx->rowpos_cap, (size_t)v->n_time + 1));
     sc.rowpos = ctx->d_rowpos;
   }
+  HIP_TRY(ctx, solve_take(ctx, s, active >= 0 && !fixed));
   hipLaunchKernelGGL(k_clear, dim3(1), dim3(64), 0, s, ctx->d_err);
   if (v->n_row > 0) {
     const long long nb = (v->n_row + 255) / 256;
@@ -318,7 +320,8 @@ qc_status qc_ctx_create(int32_t device, qc_ctx** out) {
     delete c;
     return QC_E_DEVICE;
   }
-  if (hipEventCreate(&c->ev0) != hipSuccess || hipEventCreate(&c->ev1) != hipSuccess) {
+  if (hipEventCreate(&c->ev0) != hipSuccess || hipEventCreate(&c->ev1) != hipSuccess ||
+      hipEventCreate(&c->solve_use.ev) != hipSuccess || hipEventCreate(&c->outtab_use.ev) != hipSuccess) {
     hipFree(c->d_err);
     delete c;
     return QC_E_DEVICE;
@@ -342,7 +345,6 @@ qc_status qc_ctx_destroy(qc_ctx* ctx) {
   hipFree(ctx->d_partials);
   hipFree(ctx->d_otab);
   hipFree(ctx->d_outtab);
-  if (ctx->outtab_use.ev) hipEventDestroy(ctx->outtab_use.ev);
   hipFree(ctx->d_fold);
   hipFree(ctx->d_fl_stat);
   hipFree(ctx->d_fl_groups);
@@ -369,6 +371,8 @@ qc_status qc_ctx_destroy(qc_ctx* ctx) {
   hipFree(ctx->d_ddtab);
   hipEventDestroy(ctx->ev0);
   hipEventDestroy(ctx->ev1);
+  hipEventDestroy(ctx->solve_use.ev);
+  hipEventDestroy(ctx->outtab_use.ev);
   for (hipEvent_t ev : ctx->ev_pass)
     if (ev) hipEventDestroy(ev);
   delete ctx;
@@ -389,9 +393,9 @@ const char* qc_last_error(const qc_ctx* ctx) { return ctx ? ctx->msg.c_str() : "
 
 double qc_last_kernel_ms(qc_ctx* ctx) {
   if (!ctx || !ctx->timed) return -1.0;
-  if (hipEventSynchronize(ctx->ev1) != hipSuccess) return -1.0;
+  if (hipEventSynchronize(ctx->ev_end) != hipSuccess) return -1.0;
   float ms = 0.f;
-  if (hipEventElapsedTime(&ms, ctx->ev0, ctx->ev1) != hipSuccess) return -1.0;
+  if (hipEventElapsedTime(&ms, ctx->ev0, ctx->ev_end) != hipSuccess) return -1.0;
   return (double)ms;
 }
 
@@ -581,8 +585,10 @@ static qc_status solve_interval_impl(qc_ctx* ctx, const qc_vis* vis, qc_term* ch
     st = prepare_sky(ctx, sky, vis->n_dir, uvw, s, sk);
     if (st != QC_OK) return st;
   }
-  if (chain[active].type == QC_TERM_POINTING)
+  if (chain[active].type == QC_TERM_POINTING) {
+    ctx->solve_passes = false;
     return solve_pointing(ctx, vis, chain, n_term, active, opts, stats, s);
+  }
   SolveLaunch L;
   memset(&L, 0, sizeof L);
   fill_args(vis, chain, n_term, active, L.vis, L.chain);
@@ -821,8 +827,8 @@ static qc_status solve_interval_impl(qc_ctx* ctx, const qc_vis* vis, qc_term* ch
       return fail(ctx, QC_E_UNSUPPORTED, "per-interval state needs %zu B of LDS (n_ant=%d)", lds, vis->n_ant);
     return fail(ctx, QC_E_DEVICE, "solve launch: %s", hipGetErrorString(e));
   }
-  HIP_TRY(ctx, hipEventRecord(ctx->ev1, s));
-  ctx->timed = true;
+  if (!fixed) ctx->solve_passes = parts > 1;
+  HIP_TRY(ctx, call_end(ctx, s, fixed ? nullptr : &ctx->solve_use));
   return QC_OK;
 }
 
@@ -1159,9 +1165,7 @@ static qc_status outputs_common(qc_ctx* ctx, const qc_vis* vis, const qc_term* c
     L.tab = table;
   }
   HIP_TRY(ctx, launch_outputs(L, s));
-  if (table) HIP_TRY(ctx, scratch_leave(ctx->outtab_use, s));
-  HIP_TRY(ctx, hipEventRecord(ctx->ev1, s));
-  ctx->timed = true;
+  HIP_TRY(ctx, call_end(ctx, s, table ? &ctx->outtab_use : nullptr));
   return QC_OK;
 }
 

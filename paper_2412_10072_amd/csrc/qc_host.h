@@ -36,7 +36,7 @@ constexpr int BAND_WAVES_PER_CU = 8;
 // Context scratch that a call's kernels may still read after the call returned.  A
 // call on another stream that writes it waits for them on the device.
 struct ScratchUse {
-  hipEvent_t ev = nullptr;             // after the last reader
+  hipEvent_t ev = nullptr;             // after the last reader: the call's end event (call_end)
   hipStream_t stream = nullptr;
 };
 
@@ -57,11 +57,16 @@ struct qc_ctx {
   size_t chlo_cap = 0;
   int* d_chhi = nullptr;
   size_t chhi_cap = 0;
+  // interval ranges, tables and split state of the last solve; solve_passes: of a split
+  // solve, whose last pass may still latch an error
+  ScratchUse solve_use;
+  bool solve_passes = false;
   int max_int_chan = 0;       // channels of the widest interval of the last prepared term
   std::vector<int> h_clo, h_chi;   // channel range of every interval of the last prepared term
   float* d_dh = nullptr;      // MLP backward scratch [batch][n_hid]
   size_t dh_cap = 0;
   hipEvent_t ev0 = nullptr, ev1 = nullptr;
+  hipEvent_t ev_end = nullptr;   // the last timed call's: ev1, or that of the scratch it left in use
   bool timed = false;
   int waves = 0;              // waves per workgroup of the per-interval solve (0: by the intervals)
   int rows_per_step = 0;      // 0: the kernel default
@@ -167,20 +172,24 @@ hipError_t grow(P*& ptr, size_t& cap, size_t n) {
   return hipSuccess;
 }
 
-// Before `s` writes that scratch, and after its last reader was put on `s`.
+// Before `s` writes that scratch.
 inline hipError_t scratch_take(const ScratchUse& u, hipStream_t s) {
-  return u.ev && u.stream != s ? hipStreamWaitEvent(s, u.ev, 0) : hipSuccess;
+  return u.stream != s ? hipStreamWaitEvent(s, u.ev, 0) : hipSuccess;
 }
-inline hipError_t scratch_leave(ScratchUse& u, hipStream_t s) {
-  if (!u.ev) {
-    const hipError_t e = hipEventCreateWithFlags(&u.ev, hipEventDisableTiming);
-    if (e != hipSuccess) {
-      u.ev = nullptr;
-      return e;
-    }
-  }
-  u.stream = s;
-  return hipEventRecord(u.ev, s);
+// Before a call on `s` clears the error word; writes_ranges: and rewrites the interval
+// ranges and what else a solve uses.
+inline hipError_t solve_take(const qc_ctx* ctx, hipStream_t s, bool writes_ranges) {
+  return writes_ranges || ctx->solve_passes ? scratch_take(ctx->solve_use, s) : hipSuccess;
+}
+// The end of a call's kernels on `s`, for its time and, if it leaves scratch in use,
+// for the next call that writes it: one event for both (another one costs a small
+// solve 30 of 390 us).
+inline hipError_t call_end(qc_ctx* ctx, hipStream_t s, ScratchUse* use = nullptr) {
+  ctx->ev_end = use ? use->ev : ctx->ev1;
+  if (use) use->stream = s;
+  const hipError_t e = hipEventRecord(ctx->ev_end, s);
+  ctx->timed = e == hipSuccess;
+  return e;
 }
 
 struct HostMaps {

@@ -180,8 +180,7 @@ qc_status qc_interp_term(qc_ctx* ctx, const qc_term* src, const double* t_src, c
   HIP_TRY(ctx, hipEventRecord(ctx->ev0, s));
   hipLaunchKernelGGL(k_interp, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, A);
   HIP_TRY(ctx, hipGetLastError());
-  HIP_TRY(ctx, hipEventRecord(ctx->ev1, s));
-  ctx->timed = true;
+  HIP_TRY(ctx, call_end(ctx, s));
   return QC_OK;
 }
 

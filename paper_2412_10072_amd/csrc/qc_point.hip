@@ -444,8 +444,7 @@ qc_status solve_pointing(qc_ctx* ctx, const qc_vis* vis, qc_term* chain, int n_t
     HIP_TRY(ctx, hipStreamSynchronize(s));
     if (n_active <= 0) break;
   }
-  HIP_TRY(ctx, hipEventRecord(ctx->ev1, s));
-  ctx->timed = true;
+  HIP_TRY(ctx, call_end(ctx, s, &ctx->solve_use));
   return QC_OK;
 }
 

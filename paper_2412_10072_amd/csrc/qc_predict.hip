@@ -392,6 +392,7 @@ qc_status prepare_sky(qc_ctx* ctx, const qc_sky* sky, int n_dir, const double* u
   HIP_TRY(ctx, grow(ctx->d_pc_off, ctx->pc_off_cap, off.size() + perm.size()));
   int* d_off = ctx->d_pc_off;
   int* d_perm = ctx->d_pc_off + off.size();
+  HIP_TRY(ctx, solve_take(ctx, s, false));         // (a split solve with its sky)
   HIP_TRY(ctx, hipMemcpyAsync(d_off, off.data(), off.size() * sizeof(int), hipMemcpyHostToDevice, s));
   HIP_TRY(ctx, hipMemcpyAsync(d_perm, perm.data(), perm.size() * sizeof(int), hipMemcpyHostToDevice, s));
   PComp* pc = reinterpret_cast<PComp*>(ctx->d_pc);
@@ -453,8 +454,7 @@ qc_status qc_predict_dft(qc_ctx* ctx, const double* uvw, int64_t n_row, const do
     hipLaunchKernelGGL(k_predict<double>, dim3((unsigned)blocks), dim3(256), 0, s, P, pc,
                        reinterpret_cast<double*>(model_out));
   HIP_TRY(ctx, hipGetLastError());
-  HIP_TRY(ctx, hipEventRecord(ctx->ev1, s));
-  ctx->timed = true;
+  HIP_TRY(ctx, call_end(ctx, s));
   return QC_OK;
 }
 

@@ -245,8 +245,7 @@ qc_status qc_robust_weights(qc_ctx* ctx, const qc_vis* vis, const void* resid, d
   else
     launch_rw<double>(V, resid, nu, part_sum, part_n, s2n, weight_out, s);
   HIP_TRY(ctx, hipGetLastError());
-  HIP_TRY(ctx, hipEventRecord(ctx->ev1, s));
-  ctx->timed = true;
+  HIP_TRY(ctx, call_end(ctx, s));
   if (s2_out) {
     double h[2] = {0.0, 0.0};
     HIP_TRY(ctx, hipMemcpyAsync(h, s2n, sizeof h, hipMemcpyDeviceToHost, s));

@@ -1,6 +1,7 @@
 """Calls on two streams of one context whose kernels overlap: each gives bit for
 bit what it gives alone, though both use the context's scratch memory (the outputs'
-chain table)."""
+chain table, the split
+solves' state)."""
 import sys
 
 import pytest
@@ -64,3 +65,51 @@ def test_outputs_with_tables_on_two_streams(qc_lib):
             assert torch.equal(a, out)
             out.zero_()
         torch.cuda.synchronize()
+
+
+def test_split_solves_on_two_streams(qc_lib):
+    """Solves that stop at max_iter with their last pass in flight, beside one
+    another and beside a residual: unlike sizes, so that every range, block count and
+    part differs."""
+    say("split solves on two streams")
+    probs = [device_problem(21 + i, 24 - 10 * i, 60 - 20 * i, 256 - 192 * i, 60, 128 - 64 * i) for i in range(2)]
+    start = [t.gains.clone() for _, t in probs]
+    kw = dict(tol=-1.0, prec="mixed")
+
+    def solve(i, k, **more):
+        vis, term = probs[i]
+        return qc_lib.solve(vis, [term], 0, max_iter=k, **kw, **more)
+
+    def reset():
+        torch.cuda.synchronize()
+        for (_, t), g in zip(probs, start):
+            t.gains.copy_(g)
+        torch.cuda.synchronize()
+    for k in (1, 3):
+        alone = []
+        for i in range(2):
+            st = solve(i, k)
+            assert qc_lib.last_split_parts() > 1
+            torch.cuda.synchronize()
+            alone.append((probs[i][1].gains.clone(), {n: v.clone() for n, v in st.items()}))
+        resid = qc_lib.residual(probs[1][0], [probs[1][1].copy(gains=start[1])])
+        torch.cuda.synchronize()
+        streams = [torch.cuda.Stream() for _ in range(2)]
+        out = torch.empty_like(resid)
+        for order in ((0, 1), (1, 0)):
+            reset()
+            got = {i: {n: torch.zeros_like(v) for n, v in alone[i][1].items()} for i in range(2)}
+            torch.cuda.synchronize()
+            for i in order:
+                solve(i, k, stream=streams[i], stats=got[i])
+            torch.cuda.synchronize()
+            for i in range(2):
+                assert torch.equal(probs[i][1].gains, alone[i][0])
+                for n, v in got[i].items():
+                    assert torch.equal(v, alone[i][1][n]), n
+        reset()
+        solve(0, k, stream=streams[0], stats=got[0])
+        qc_lib.residual(probs[1][0], [probs[1][1]], out=out, stream=streams[1])
+        torch.cuda.synchronize()
+        assert torch.equal(out, resid) and torch.equal(probs[0][1].gains, alone[0][0])
+        reset()
