@@ -170,6 +170,11 @@ qc_status   qc_ctx_set_tile(qc_ctx* ctx, int32_t waves, int32_t rows_per_step);
 qc_status   qc_ctx_set_split(qc_ctx* ctx, int32_t parts);
 /* Parts per interval of the last qc_solve_interval (1 = not split). */
 int32_t     qc_ctx_last_split(const qc_ctx* ctx);
+/* How the last qc_solve_interval ran, as bits; -1 for a NULL context. */
+#define QC_ROUTE_SPLIT 1    /* the split schedule                                       */
+#define QC_ROUTE_FOLD  2    /* over the fixed terms and directions folded into one model */
+#define QC_ROUTE_BAND  4    /* several one-channel intervals per wavefront              */
+int32_t     qc_ctx_last_route(const qc_ctx* ctx);
 
 /* One visibility set (paper Section 2.2; data model of Section 4.1). */
 typedef struct {
@@ -548,6 +553,10 @@ double    qc_batch_last_ms(qc_batch* batch);
  * work items, waves per workgroup, rows per step, tuned time (ms, < 0 if untuned). */
 qc_status qc_batch_schedule(const qc_batch* batch, int32_t* items, int32_t* waves, int32_t* rows_per_step,
                             float* tuned_ms, int32_t n);
+/* Intervals that teams of workgroups share (a part of the buckets' items), -1 for a
+ * NULL batch; parts (may be NULL): the row parts of the first n of them, largest
+ * interval first. */
+int32_t   qc_batch_teams(const qc_batch* batch, int32_t* parts, int32_t n);
 qc_status qc_batch_destroy(qc_batch* batch);
 /* Learned warm start over a batch (the growth direction of the warm start;
  * no paper passage): the feature pass of qc_ws_features and the gain write

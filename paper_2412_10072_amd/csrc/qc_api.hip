@@ -699,6 +699,7 @@ static qc_status solve_interval_impl(qc_ctx* ctx, const qc_vis* vis, qc_term* ch
     parts = std::max(2, std::min(parts, (int)std::max(1.0, rows_per_int / 32.0)));
   }
   ctx->last_split_parts = parts;
+  ctx->last_route = (parts > 1 ? QC_ROUTE_SPLIT : 0) | (fold ? QC_ROUTE_FOLD : 0) | (band ? QC_ROUTE_BAND : 0);
   // diagonal chains: the direction-independent terms other than the active
   // one are fixed during the solve; tabulate their product once
   bool other_di = false;
@@ -862,6 +863,8 @@ qc_status qc_solve_interval_static(qc_ctx* ctx, const qc_vis* vis, qc_term* chai
 }
 
 int32_t qc_ctx_last_split(const qc_ctx* ctx) { return ctx ? ctx->last_split_parts : -1; }
+
+int32_t qc_ctx_last_route(const qc_ctx* ctx) { return ctx ? ctx->last_route : -1; }
 
 qc_status qc_ctx_set_split(qc_ctx* ctx, int32_t parts) {
   if (!ctx) return QC_E_ARG;

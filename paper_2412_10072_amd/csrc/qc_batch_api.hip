@@ -74,6 +74,7 @@ struct qc_batch {
   // intervals solved by teams of workgroups (the first n_team of d_items)
   int n_team = 0, team_grid = 0;
   size_t team_lds = 0;
+  std::vector<int> team_parts;
   TeamItem* d_team = nullptr;
   TeamWords* d_team_words = nullptr;
   double* d_team_parts = nullptr;
@@ -181,6 +182,7 @@ qc_status make_team(qc_batch* b, const std::vector<BatchItem>& items) {
     t.dv_off = dv;
     dv += 2LL * P.vis.n_ant;
     n_parts += t.n_part;
+    b->team_parts.push_back(t.n_part);
   }
   if (hipMalloc(reinterpret_cast<void**>(&b->d_team), sizeof(TeamItem) * team.size()) != hipSuccess ||
       hipMalloc(reinterpret_cast<void**>(&b->d_team_words), sizeof(TeamWords) * (team.size() + 1)) != hipSuccess ||
@@ -549,6 +551,12 @@ qc_status qc_batch_schedule(const qc_batch* b, int32_t* items, int32_t* waves, i
     if (tuned_ms) tuned_ms[i] = b->bucket[i].ms;
   }
   return QC_OK;
+}
+
+int32_t qc_batch_teams(const qc_batch* b, int32_t* parts, int32_t n) {
+  if (!b) return -1;
+  for (int k = 0; parts && k < std::min(n, b->n_team); ++k) parts[k] = b->team_parts[k];
+  return b->n_team;
 }
 
 qc_status qc_batch_destroy(qc_batch* b) {

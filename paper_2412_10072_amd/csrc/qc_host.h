@@ -130,6 +130,7 @@ struct qc_ctx {
   unsigned char* d_ddtab = nullptr;    // that split: tables of the direction-dependent fixed terms
   size_t ddtab_cap = 0;
   int last_split_parts = 1;   // parts per interval of the last solve (1 = fused)
+  int last_route = 0;         // QC_ROUTE_* of the last solve
   unsigned char* static_scratch = nullptr;   // this device's allocation-free scratch array (qc_api.hip)
 };
 

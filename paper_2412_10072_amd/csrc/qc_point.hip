@@ -381,6 +381,7 @@ qc_status solve_pointing(qc_ctx* ctx, const qc_vis* vis, qc_term* chain, int n_t
   }
   L.n_part = parts;
   ctx->last_split_parts = parts;
+  ctx->last_route = QC_ROUTE_SPLIT;
   L.row_lo = ctx->d_rowlo;
   L.row_hi = ctx->d_rowhi;
   L.chan_lo = ctx->d_chlo;

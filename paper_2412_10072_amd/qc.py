@@ -30,13 +30,14 @@ PRECISIONS = {"fp64": 0, "mixed": 1}
 DAMPINGS = {"full": 0, "half": 1, "alternate": 2, "auto": 3, "lm": 4}
 
 EXPORTS = ("qc_ctx_create", "qc_ctx_destroy", "qc_ctx_sync", "qc_last_error", "qc_last_kernel_ms", "qc_ctx_set_tile",
-           "qc_ctx_set_split", "qc_ctx_last_split",
+           "qc_ctx_set_split", "qc_ctx_last_split", "qc_ctx_last_route", "qc_batch_teams",
            "qc_solve_interval", "qc_solve_interval_static", "qc_solve_chain", "qc_delay_init", "qc_apply_gains", "qc_residual",
            "qc_batch_create", "qc_batch_tune", "qc_batch_run", "qc_batch_last_ms", "qc_batch_schedule",
            "qc_batch_destroy", "qc_solve_batch", "qc_ws_features", "qc_mlp_forward", "qc_mlp_backward",
            "qc_adam_step", "qc_mse_grad", "qc_ws_gains", "qc_ws_labels", "qc_mad_flag", "qc_predict_dft", "qc_robust_weights",
            "qc_corrected_weights", "qc_solve_chain_robust", "qc_interp_term", "qc_solve_interval_sky",
            "qc_residual_sky", "qc_corrupt_sky", "qc_batch_n_intervals", "qc_batch_ws_features", "qc_batch_ws_gains")
+ROUTE_SPLIT, ROUTE_FOLD, ROUTE_BAND = 1, 2, 4
 MAD_MODES = {"global": 0, "baseline": 1}
 BATCH_BUCKETS = 6
 
@@ -112,6 +113,8 @@ def load_library(path: str = LIB_PATH) -> C.CDLL:
     lib.qc_ctx_set_split.argtypes = [C.c_void_p, C.c_int32]
     lib.qc_ctx_last_split.argtypes = [C.c_void_p]
     lib.qc_ctx_last_split.restype = C.c_int32
+    lib.qc_ctx_last_route.argtypes = [C.c_void_p]
+    lib.qc_batch_teams.argtypes = [C.c_void_p, C.c_void_p, C.c_int32]
     lib.qc_solve_chain.argtypes = [C.c_void_p, C.POINTER(QcVis), C.POINTER(QcTerm), C.c_int32, C.c_int32,
                                    C.POINTER(QcSolveOpts), C.c_void_p]
     lib.qc_delay_init.argtypes = [C.c_void_p, C.POINTER(QcVis), C.POINTER(QcTerm), C.c_int32, C.c_void_p]
@@ -379,6 +382,10 @@ class Context:
 
     def last_split_parts(self) -> int:
         return int(self.lib.qc_ctx_last_split(self.h))
+
+    def last_route(self) -> int:
+        """qc_ctx_last_route: ROUTE_* bits of the last solve."""
+        return int(self.lib.qc_ctx_last_route(self.h))
 
     def last_kernel_ms(self) -> float:
         return float(self.lib.qc_last_kernel_ms(self.h))
@@ -777,6 +784,13 @@ class Batch:
         self.ctx._check(self.lib.qc_batch_schedule(self.h, items, waves, rps, ms, n))
         return [dict(items=items[i], waves=waves[i], rows_per_step=rps[i], tuned_ms=float(ms[i]))
                 for i in range(n)]
+
+    def teams(self):
+        """qc_batch_teams: row parts of every interval that a team of workgroups shares."""
+        n = int(self.lib.qc_batch_teams(self.h, None, 0))
+        parts = (C.c_int32 * max(n, 1))()
+        self.lib.qc_batch_teams(self.h, parts, n)
+        return list(parts[:n])
 
     def close(self):
         if getattr(self, "h", None):
