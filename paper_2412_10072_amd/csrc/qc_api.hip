@@ -644,31 +644,38 @@ static qc_status solve_interval_impl(qc_ctx* ctx, const qc_vis* vis, qc_term* ch
   bool one_chan = ta.type == QC_TERM_DIAGONAL && ctx->max_int_chan == 1 && ta.n_gf == vis->n_chan;
   for (int g = 0; one_chan && g < ta.n_gf; ++g)
     if (ctx->h_clo[g] != g) one_chan = false;
+  // intervals of one channel each, in channel order, on a diagonal chain with
+  // one gain direction: the split pass over 16 channels per wavefront
+  bool band = !sky && L.diag_chain && !L.left_general && one_chan && ta.n_gdir == 1 && vis->n_row < (1LL << 31) &&
+              band_lds_bytes_for(vis->n_ant, 8) <= (L.prec_mixed ? 160 : 64) * 1024;
   // A diagonal chain whose active term has one gain direction: folded into one
   // model where several passes will read it, the model is stored as it is
   // computed (MIXED of complex64, FP64 of complex128) and the memory is there.
-  // (Levenberg-Marquardt keeps its arithmetic; intervals of 2 to 4 channels keep
-  // the one-row-per-lane kernel of chains.)
+  // (Levenberg-Marquardt keeps its arithmetic.  Intervals of up to 4 channels keep
+  // the one-row-per-lane kernel of chains unless the band pass takes them: the
+  // single-term kernels read a row's channels on 16 lanes.)
   bool fold = !fixed && !sky && !lm && L.diag_chain && !single_chain && ta.n_gdir == 1 && opts->max_iter >= 3 &&
-              L.prec_mixed != L.vis_is_c128 && (one_chan || ctx->max_int_chan > 4);
-  if (fold) fold = spare_memory(ctx, ctx->d_fold, ctx->fold_cap, chain_fold_bytes(L));
+              L.prec_mixed != L.vis_is_c128 && (band || ctx->max_int_chan > 4);
   if (lm && ta.type == QC_TERM_DELAY_OFFSET)
     return fail(ctx, QC_E_UNSUPPORTED, "Levenberg-Marquardt takes no delay-and-offset term");
-  const PassShape shape = pass_shape(ctx, vis, ta, single_chain || fold, L);
-  const int waves = ctx->waves ? ctx->waves : fused_waves(ctx, shape, single_chain || fold, lm);
-  if (fixed) {
-    parts = 1;                                 // the split schedule's state is context memory
-  } else if (ctx->split_parts > 1) {
-    parts = ctx->split_parts;
-  } else if (ctx->split_parts == 0 && !opts->chisq_ref && n_int > 0) {
-    parts = split_parts(ctx, vis, ta, shape, waves, lm);
+  int waves = 4;
+  auto choose = [&]() {
+    const bool single = single_chain || (fold && !band);
+    const PassShape shape = pass_shape(ctx, vis, ta, single, L);
+    waves = ctx->waves ? ctx->waves : fused_waves(ctx, shape, single, lm);
+    parts = 1;
+    if (fixed) return;                         // the split schedule's state is context memory
+    if (ctx->split_parts > 1) parts = ctx->split_parts;
+    else if (ctx->split_parts == 0 && !opts->chisq_ref && n_int > 0) parts = split_parts(ctx, vis, ta, shape, waves, lm);
+  };
+  choose();
+  if (fold && ((band && parts == 1) || !spare_memory(ctx, ctx->d_fold, ctx->fold_cap, chain_fold_bytes(L)))) {
+    fold = false;
+    choose();
   }
   if (parts > 1 && opts->chisq_ref)
     return fail(ctx, QC_E_UNSUPPORTED, "the split schedule does not take chisq_ref");
-  // intervals of one channel each, in channel order, on a diagonal chain with
-  // one gain direction: the split pass over 16 channels per wavefront
-  bool band = parts > 1 && !sky && L.diag_chain && !L.left_general && one_chan && ta.n_gdir == 1 &&
-              vis->n_row < (1LL << 31) && band_lds_bytes_for(vis->n_ant, 8) <= (L.prec_mixed ? 160 : 64) * 1024;
+  band = band && parts > 1;
   // diagonal chains: the direction-dependent fixed terms, when all are
   // diagonal gains and at most BAND_MAX_DD, tabulated once per solve for every
   // pass (the band pass takes no other kind).  A pointing term differs by

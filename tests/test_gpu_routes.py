@@ -97,7 +97,7 @@ def test_band_pass_over_an_unfolded_chain(ctx, dtype, prec, k, n_dd, rows):
 
 @pytest.mark.parametrize("n_dd", [0, 2])
 @pytest.mark.parametrize("dtype,prec", [("c64", "mixed"), ("c128", "fp64"), ("c64", "fp64")])
-@pytest.mark.parametrize("f_int", [3, 21])
+@pytest.mark.parametrize("f_int", [1, 3, 21])
 def test_folded_and_unfolded_chains(ctx, f_int, dtype, prec, n_dd):
     """Fewer than three updates and FP64 over complex64 leave the chain unfolded."""
     from paper_2412_10072_amd import qc
