@@ -475,6 +475,16 @@ static int fused_waves(const qc_ctx* ctx, const PassShape& S, bool single, bool 
   return 4;
 }
 
+// Values of one part's sums: every block's (qc_interval.h: KindInfo NV, or NV_FB for full
+// blocks) and chi^2.
+static size_t split_values(const qc_vis* vis, const qc_term& ta, bool left_general) {
+  const int nv = left_general ? (ta.type == QC_TERM_DIAGONAL ? 8
+                                 : ta.type == QC_TERM_COMPLEX2X2 ? 24 : (ta.type == QC_TERM_DELAY_OFFSET ? 14 : 5))
+                              : (ta.type == QC_TERM_DIAGONAL ? 6
+                                 : ta.type == QC_TERM_COMPLEX2X2 ? 16 : (ta.type == QC_TERM_DELAY_OFFSET ? 10 : 4));
+  return (size_t)vis->n_ant * (ta.n_gdir == 1 ? 1 : 4) * nv + 1;
+}
+
 // Parts per interval of a solve (1: the fused schedule), by an estimate of
 // one pass of each schedule in microseconds.
 //
@@ -497,7 +507,8 @@ static int fused_waves(const qc_ctx* ctx, const PassShape& S, bool single, bool 
 // workgroups over a round run on an empty one.  80 full-Jones intervals take 1.82 ms in
 // 13 parts each (1040 workgroups of 1024 at once), 1.50 in 8; 190 FP64 ones 4.47 ms in
 // 6 (1140 of 512), 4.07 in 8 (1520).
-static int split_parts(const qc_ctx* ctx, const qc_vis* vis, const qc_term& ta, const PassShape& S, int waves, bool lm) {
+static int split_parts(const qc_ctx* ctx, const qc_vis* vis, const qc_term& ta, const PassShape& S, int waves, bool lm,
+                       bool left_general) {
   const int n_int = S.n_int;
   const bool large = n_int < 4 * ctx->n_cu && S.avg >= (double)(1 << 18);   // split whatever the estimate
   if (lm && !large) return 1;
@@ -521,9 +532,7 @@ static int split_parts(const qc_ctx* ctx, const qc_vis* vis, const qc_term& ta, 
       parts = p;
     }
   }
-  // the partial sums (24 values per block at most) stay below 2 GiB
-  const double blocks = (double)n_int * parts * vis->n_ant * (ta.n_gdir == 1 ? 1 : 4);
-  return blocks * 24.0 * sizeof(double) > 2147483648.0 ? 1 : parts;
+  return split_parts_within(parts, n_int, split_values(vis, ta, left_general));
 }
 
 // Memory of the context that a call can do without (spare_fits); false: the call goes
@@ -666,7 +675,7 @@ static qc_status solve_interval_impl(qc_ctx* ctx, const qc_vis* vis, qc_term* ch
     parts = 1;
     if (fixed) return;                         // the split schedule's state is context memory
     if (ctx->split_parts > 1) parts = ctx->split_parts;
-    else if (ctx->split_parts == 0 && !opts->chisq_ref && n_int > 0) parts = split_parts(ctx, vis, ta, shape, waves, lm);
+    else if (ctx->split_parts == 0 && !opts->chisq_ref && n_int > 0) parts = split_parts(ctx, vis, ta, shape, waves, lm, L.left_general != 0);
   };
   choose();
   if (fold && ((band && parts == 1) || !spare_memory(ctx, ctx->d_fold, ctx->fold_cap, chain_fold_bytes(L)))) {
@@ -717,13 +726,8 @@ static qc_status solve_interval_impl(qc_ctx* ctx, const qc_vis* vis, qc_term* ch
   if (want_tab) HIP_TRY(ctx, grow(ctx->d_otab, ctx->otab_cap, chain_table_bytes(L)));
   SplitLaunch P;
   if (parts > 1) {
-    // values per block (qc_interval.h: KindInfo NV, or NV_FB for full blocks)
-    const int nv = L.left_general ? (ta.type == QC_TERM_DIAGONAL ? 8
-                                     : ta.type == QC_TERM_COMPLEX2X2 ? 24 : (ta.type == QC_TERM_DELAY_OFFSET ? 14 : 5))
-                                  : (ta.type == QC_TERM_DIAGONAL ? 6
-                                     : ta.type == QC_TERM_COMPLEX2X2 ? 16 : (ta.type == QC_TERM_DELAY_OFFSET ? 10 : 4));
     const int ng = ta.n_gdir == 1 ? 1 : 4;
-    const size_t stride = (size_t)vis->n_ant * ng * nv + 1;
+    const size_t stride = split_values(vis, ta, L.left_general != 0);
     HIP_TRY(ctx, grow(ctx->d_partials, ctx->partials_cap, stride * (size_t)n_int * parts));
     HIP_TRY(ctx, grow(ctx->d_passes, ctx->passes_cap, (size_t)n_int));
     HIP_TRY(ctx, grow(ctx->d_done, ctx->done_cap, (size_t)n_int));

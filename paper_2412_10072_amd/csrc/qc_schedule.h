@@ -2,6 +2,7 @@
 // HIP, so that the same code also builds on its own in a CPU test.
 #pragma once
 
+#include <algorithm>
 #include <cstddef>
 
 namespace qc {
@@ -11,6 +12,15 @@ namespace qc {
 // arrays the caller may still want come first).
 inline bool spare_fits(size_t bytes, size_t free_b, size_t total_b) {
   return bytes > 0 && bytes <= total_b / 16 && bytes <= free_b / 8;
+}
+
+// Parts per interval whose partial sums (`values` doubles each, of n_int intervals) stay
+// within SPLIT_SUMS_BYTES: as many of `parts` as fit, 1 (not split) if not even two do.
+constexpr double SPLIT_SUMS_BYTES = 2147483648.0;
+inline int split_parts_within(int parts, int n_int, size_t values) {
+  const double one = (double)n_int * (double)values * sizeof(double);
+  const int fit = (int)std::min(SPLIT_SUMS_BYTES / std::max(one, 1.0), (double)parts);
+  return fit >= 2 ? fit : 1;
 }
 
 }  // namespace qc

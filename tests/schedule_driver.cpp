@@ -24,8 +24,21 @@ static void spare_cases() {
   EXPECT(!qc::spare_fits(0, 288 * GiB, 288 * GiB));                // nothing to hold
 }
 
+static void parts_cases() {
+  // 64 antennas, one gain direction, 6 values a block: nothing to cut
+  EXPECT(qc::split_parts_within(512, 1, 64 * 6 + 1) == 512);
+  // 256 antennas, four gain directions, full blocks: fewer parts, not none
+  const size_t wide = 256 * 4 * 24 + 1;
+  const int p = qc::split_parts_within(16384, 1, wide);
+  EXPECT(p > 10000 && (double)p * wide * 8 <= qc::SPLIT_SUMS_BYTES && (double)(p + 1) * wide * 8 > qc::SPLIT_SUMS_BYTES);
+  EXPECT(qc::split_parts_within(12, 1000, wide) == 10);
+  EXPECT(qc::split_parts_within(2, 100000, wide) == 1);      // not even two parts fit
+  EXPECT(qc::split_parts_within(1, 1, wide) == 1);
+}
+
 int main() {
   spare_cases();
+  parts_cases();
   std::printf("%d failures\n", failures);
   return failures == 0 ? 0 : 1;
 }
