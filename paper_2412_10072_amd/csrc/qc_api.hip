@@ -507,8 +507,7 @@ static size_t split_values(const qc_vis* vis, const qc_term& ta, bool left_gener
 // workgroups over a round run on an empty one.  80 full-Jones intervals take 1.82 ms in
 // 13 parts each (1040 workgroups of 1024 at once), 1.50 in 8; 190 FP64 ones 4.47 ms in
 // 6 (1140 of 512), 4.07 in 8 (1520).
-static int split_parts(const qc_ctx* ctx, const qc_vis* vis, const qc_term& ta, const PassShape& S, int waves, bool lm,
-                       bool left_general) {
+static int split_parts(const qc_ctx* ctx, const qc_vis* vis, const qc_term& ta, const PassShape& S, int waves, bool lm) {
   const int n_int = S.n_int;
   const bool large = n_int < 4 * ctx->n_cu && S.avg >= (double)(1 << 18);   // split whatever the estimate
   if (lm && !large) return 1;
@@ -532,7 +531,29 @@ static int split_parts(const qc_ctx* ctx, const qc_vis* vis, const qc_term& ta, 
       parts = p;
     }
   }
-  return split_parts_within(parts, n_int, split_values(vis, ta, left_general));
+  return parts;
+}
+
+// Wavefronts' parts of the band pass per gain time: BAND_WAVES_PER_CU of them per compute
+// unit, or as many as its LDS holds.
+static int band_parts(const qc_ctx* ctx, const qc_vis* vis, const qc_term& ta, int rows) {
+  const long long units = (long long)((vis->n_chan + 64 / rows - 1) / (64 / rows)) * ta.n_gt;
+  const double rows_per_int = (double)vis->n_row / std::max(ta.n_gt, 1);
+  const int fit = (int)(160 * 1024 / band_lds_bytes_for(vis->n_ant, rows));
+  const int parts = (int)((long long)std::max(1, std::min(BAND_WAVES_PER_CU, fit)) * ctx->n_cu / units);
+  return std::max(2, std::min(parts, (int)std::max(1.0, rows_per_int / 32.0)));
+}
+
+// The parts that the memory for their sums allows (split_parts_within).
+static int parts_in_memory(const qc_ctx* ctx, int parts, int n_int, size_t values) {
+  const size_t held = ctx->d_partials ? ctx->partials_cap * sizeof(double) : 0;
+  size_t free_b = 0, total_b = 0;
+  if ((double)parts * n_int * (double)values * sizeof(double) > (double)held &&
+      hipMemGetInfo(&free_b, &total_b) != hipSuccess) {
+    (void)hipGetLastError();
+    free_b = 0;
+  }
+  return split_parts_within(parts, n_int, values, held, free_b);
 }
 
 // Memory of the context that a call can do without (spare_fits); false: the call goes
@@ -653,38 +674,6 @@ static qc_status solve_interval_impl(qc_ctx* ctx, const qc_vis* vis, qc_term* ch
   bool one_chan = ta.type == QC_TERM_DIAGONAL && ctx->max_int_chan == 1 && ta.n_gf == vis->n_chan;
   for (int g = 0; one_chan && g < ta.n_gf; ++g)
     if (ctx->h_clo[g] != g) one_chan = false;
-  // intervals of one channel each, in channel order, on a diagonal chain with
-  // one gain direction: the split pass over 16 channels per wavefront
-  bool band = !sky && L.diag_chain && !L.left_general && one_chan && ta.n_gdir == 1 && vis->n_row < (1LL << 31) &&
-              band_lds_bytes_for(vis->n_ant, 8) <= (L.prec_mixed ? 160 : 64) * 1024;
-  // A diagonal chain whose active term has one gain direction: folded into one
-  // model where several passes will read it, the model is stored as it is
-  // computed (MIXED of complex64, FP64 of complex128) and the memory is there.
-  // (Levenberg-Marquardt keeps its arithmetic.  Intervals of up to 4 channels keep
-  // the one-row-per-lane kernel of chains unless the band pass takes them: the
-  // single-term kernels read a row's channels on 16 lanes.)
-  bool fold = !fixed && !sky && !lm && L.diag_chain && !single_chain && ta.n_gdir == 1 && opts->max_iter >= 3 &&
-              L.prec_mixed != L.vis_is_c128 && (band || ctx->max_int_chan > 4);
-  if (lm && ta.type == QC_TERM_DELAY_OFFSET)
-    return fail(ctx, QC_E_UNSUPPORTED, "Levenberg-Marquardt takes no delay-and-offset term");
-  int waves = 4;
-  auto choose = [&]() {
-    const bool single = single_chain || (fold && !band);
-    const PassShape shape = pass_shape(ctx, vis, ta, single, L);
-    waves = ctx->waves ? ctx->waves : fused_waves(ctx, shape, single, lm);
-    parts = 1;
-    if (fixed) return;                         // the split schedule's state is context memory
-    if (ctx->split_parts > 1) parts = ctx->split_parts;
-    else if (ctx->split_parts == 0 && !opts->chisq_ref && n_int > 0) parts = split_parts(ctx, vis, ta, shape, waves, lm, L.left_general != 0);
-  };
-  choose();
-  if (fold && ((band && parts == 1) || !spare_memory(ctx, ctx->d_fold, ctx->fold_cap, chain_fold_bytes(L)))) {
-    fold = false;
-    choose();
-  }
-  if (parts > 1 && opts->chisq_ref)
-    return fail(ctx, QC_E_UNSUPPORTED, "the split schedule does not take chisq_ref");
-  band = band && parts > 1;
   // diagonal chains: the direction-dependent fixed terms, when all are
   // diagonal gains and at most BAND_MAX_DD, tabulated once per solve for every
   // pass (the band pass takes no other kind).  A pointing term differs by
@@ -698,7 +687,20 @@ static qc_status solve_interval_impl(qc_ctx* ctx, const qc_vis* vis, qc_term* ch
     else L.dd_term[L.n_dd++] = j;
   }
   if (!L.dd_tabled) L.n_dd = 0;
-  if (!L.dd_tabled && !fold) band = false;
+  // A diagonal chain whose active term has one gain direction: folded into one
+  // model where several passes will read it, the model is stored as it is
+  // computed (MIXED of complex64, FP64 of complex128) and the memory is there.
+  // (Levenberg-Marquardt keeps its arithmetic.  Intervals of up to 4 channels keep
+  // the one-row-per-lane kernel of chains unless the band pass takes them: the
+  // single-term kernels read a row's channels on 16 lanes.)
+  bool fold = !fixed && !sky && !lm && L.diag_chain && !single_chain && ta.n_gdir == 1 && opts->max_iter >= 3 &&
+              L.prec_mixed != L.vis_is_c128;
+  // intervals of one channel each, in channel order, on a diagonal chain with
+  // one gain direction: the split pass over 16 channels per wavefront
+  const bool band_fits = !sky && L.diag_chain && !L.left_general && one_chan && ta.n_gdir == 1 && vis->n_row < (1LL << 31) &&
+                         band_lds_bytes_for(vis->n_ant, 8) <= (L.prec_mixed ? 160 : 64) * 1024;
+  bool band = band_fits && (L.dd_tabled || fold);
+  fold = fold && (band || ctx->max_int_chan > 4);
   // 4 rows x 16 channels per step, or as asked; 8 x 8, whose LDS slots are half as
   // large, where those do not fit and, in MIXED, where they leave a compute unit
   // fewer than six wavefronts (solves of 10 updates, 4 x 16 / 8 x 8: 28 antennas, 100
@@ -707,13 +709,32 @@ static qc_status solve_interval_impl(qc_ctx* ctx, const qc_vis* vis, qc_term* ch
   const size_t rows4 = band_lds_bytes_for(vis->n_ant, 4);
   L.band_rows = (ctx->rows_per_step == 8 || rows4 > 64 * 1024 ||
                  (L.prec_mixed && ctx->rows_per_step != 4 && rows4 > 160 * 1024 / 6)) ? 8 : 4;
-  if (band && ctx->split_parts == 0) {
-    const long long units = (long long)((vis->n_chan + 64 / L.band_rows - 1) / (64 / L.band_rows)) * ta.n_gt;
-    const double rows_per_int = (double)vis->n_row / std::max(ta.n_gt, 1);
-    const int fit = (int)(160 * 1024 / band_lds_bytes_for(vis->n_ant, L.band_rows));
-    parts = (int)((long long)std::max(1, std::min(BAND_WAVES_PER_CU, fit)) * ctx->n_cu / units);
-    parts = std::max(2, std::min(parts, (int)std::max(1.0, rows_per_int / 32.0)));
+  if (lm && ta.type == QC_TERM_DELAY_OFFSET)
+    return fail(ctx, QC_E_UNSUPPORTED, "Levenberg-Marquardt takes no delay-and-offset term");
+  int waves = 4;
+  auto choose = [&]() {
+    const bool single = single_chain || (fold && !band);
+    const PassShape shape = pass_shape(ctx, vis, ta, single, L);
+    waves = ctx->waves ? ctx->waves : fused_waves(ctx, shape, single, lm);
+    parts = 1;
+    if (fixed) return;                         // the split schedule's state is context memory
+    if (ctx->split_parts > 1) {
+      parts = ctx->split_parts;
+    } else if (ctx->split_parts == 0 && !opts->chisq_ref && n_int > 0) {
+      parts = split_parts(ctx, vis, ta, shape, waves, lm);
+      if (parts > 1 && band) parts = band_parts(ctx, vis, ta, L.band_rows);
+      if (parts > 1) parts = parts_in_memory(ctx, parts, n_int, split_values(vis, ta, L.left_general != 0));
+    }
+  };
+  choose();
+  if (fold && ((band && parts == 1) || !spare_memory(ctx, ctx->d_fold, ctx->fold_cap, chain_fold_bytes(L)))) {
+    fold = false;
+    band = band_fits && L.dd_tabled;
+    choose();
   }
+  if (parts > 1 && opts->chisq_ref)
+    return fail(ctx, QC_E_UNSUPPORTED, "the split schedule does not take chisq_ref");
+  band = band && parts > 1;
   ctx->last_split_parts = parts;
   ctx->last_route = (parts > 1 ? QC_ROUTE_SPLIT : 0) | (fold ? QC_ROUTE_FOLD : 0) | (band ? QC_ROUTE_BAND : 0);
   // diagonal chains: the direction-independent terms other than the active

@@ -25,15 +25,23 @@ static void spare_cases() {
 }
 
 static void parts_cases() {
+  const size_t GiB = (size_t)1 << 30, much = 200 * GiB;
   // 64 antennas, one gain direction, 6 values a block: nothing to cut
-  EXPECT(qc::split_parts_within(512, 1, 64 * 6 + 1) == 512);
+  EXPECT(qc::split_parts_within(512, 1, 64 * 6 + 1, 0, much) == 512);
   // 256 antennas, four gain directions, full blocks: fewer parts, not none
   const size_t wide = 256 * 4 * 24 + 1;
-  const int p = qc::split_parts_within(16384, 1, wide);
+  const int p = qc::split_parts_within(16384, 1, wide, 0, much);
   EXPECT(p > 10000 && (double)p * wide * 8 <= qc::SPLIT_SUMS_BYTES && (double)(p + 1) * wide * 8 > qc::SPLIT_SUMS_BYTES);
-  EXPECT(qc::split_parts_within(12, 1000, wide) == 10);
-  EXPECT(qc::split_parts_within(2, 100000, wide) == 1);      // not even two parts fit
-  EXPECT(qc::split_parts_within(1, 1, wide) == 1);
+  EXPECT(qc::split_parts_within(12, 1000, wide, 0, much) == 10);
+  EXPECT(qc::split_parts_within(2, 100000, wide, 0, much) == 1);      // not even two parts fit
+  EXPECT(qc::split_parts_within(1, 1, wide, 0, much) == 1);
+  // half of what is free, unless the context holds more: fewer parts, then the
+  // fused schedule instead of an allocation that fails
+  EXPECT(qc::split_parts_within(1024, 4, 1000, 0, 64000000) == 1000);
+  EXPECT(qc::split_parts_within(1024, 4, 1000, 0, 1000000) == 15);
+  EXPECT(qc::split_parts_within(1024, 4, 1000, 0, 100000) == 1);
+  EXPECT(qc::split_parts_within(1024, 4, 1000, 0, 0) == 1);
+  EXPECT(qc::split_parts_within(1024, 4, 1000, 1024 * 32000, 0) == 1024);
 }
 
 int main() {
