@@ -7,6 +7,7 @@
 #include <numeric>
 
 #include "qc_batch.h"
+#include "qc_schedule.h"
 #include "qc_host.h"
 #include "qc_hostcheck.h"
 
@@ -158,7 +159,20 @@ void choose_team(const qc_batch* b, const std::vector<BatchItem>& items, std::ve
   }
 }
 
-// The team items (the first n_team of `items`), their parts and device memory.
+void drop_team(qc_batch* b) {
+  hipFree(b->d_team);
+  hipFree(b->d_team_words);
+  hipFree(b->d_team_parts);
+  hipFree(b->d_team_dv);
+  b->d_team = nullptr;
+  b->d_team_words = nullptr;
+  b->d_team_parts = nullptr;
+  b->d_team_dv = nullptr;
+  b->team_parts.clear();
+}
+
+// The team items (the first n_team of `items`), their parts and device memory;
+// QC_E_NOMEM (and nothing kept) where the device has no spare memory for them.
 qc_status make_team(qc_batch* b, const std::vector<BatchItem>& items) {
   qc_ctx* ctx = b->ctx;
   if (b->n_team == 0) return QC_OK;
@@ -184,11 +198,17 @@ qc_status make_team(qc_batch* b, const std::vector<BatchItem>& items) {
     n_parts += t.n_part;
     b->team_parts.push_back(t.n_part);
   }
-  if (hipMalloc(reinterpret_cast<void**>(&b->d_team), sizeof(TeamItem) * team.size()) != hipSuccess ||
+  size_t free_b = 0, total_b = 0;
+  HIP_TRY(ctx, hipMemGetInfo(&free_b, &total_b));
+  if (!spare_fits(sizeof(double) * (size_t)(parts + dv), free_b, total_b) ||
+      hipMalloc(reinterpret_cast<void**>(&b->d_team), sizeof(TeamItem) * team.size()) != hipSuccess ||
       hipMalloc(reinterpret_cast<void**>(&b->d_team_words), sizeof(TeamWords) * (team.size() + 1)) != hipSuccess ||
       hipMalloc(reinterpret_cast<void**>(&b->d_team_parts), sizeof(double) * parts) != hipSuccess ||
-      hipMalloc(reinterpret_cast<void**>(&b->d_team_dv), sizeof(double) * dv) != hipSuccess)
+      hipMalloc(reinterpret_cast<void**>(&b->d_team_dv), sizeof(double) * dv) != hipSuccess) {
+    (void)hipGetLastError();
+    drop_team(b);
     return fail(ctx, QC_E_NOMEM, "batch team memory");
+  }
   HIP_TRY(ctx, hipMemcpy(b->d_team, team.data(), sizeof(TeamItem) * team.size(), hipMemcpyHostToDevice));
   void* kern = team_kernel_ptr(b->prec_mixed, b->vis_c128);
   b->team_lds = team_lds_bytes(b->prec_mixed, b->max_ant);
@@ -199,6 +219,39 @@ qc_status make_team(qc_batch* b, const std::vector<BatchItem>& items) {
   HIP_TRY(ctx, hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, 256, b->team_lds));
   b->team_grid = (int)std::min<long long>(n_parts, (long long)b->n_cu * std::max(per_cu, 1));
   return QC_OK;
+}
+
+// `items` in the order of the plan: the teams' (`team`) first, then bucket after bucket,
+// the largest of each first.
+void arrange(qc_batch* b, const std::vector<BatchItem>& items, const std::vector<char>& team,
+             std::vector<BatchItem>& sorted) {
+  b->n_team = 0;
+  for (Bucket& bk : b->bucket) bk.count = bk.team = 0;
+  std::vector<int> key(items.size());
+  std::vector<long long> size(items.size());
+  for (size_t k = 0; k < items.size(); ++k) {
+    const BatchItem& it = items[k];
+    const long long smp = (it.r_hi - it.r_lo) * (long long)(it.c_hi - it.c_lo);
+    size[k] = smp * (b->probs[it.prob].term.kind == KIND_C2X2 ? 2 : 1);
+    key[k] = width_class(it.c_hi - it.c_lo) * N_SIZE + (smp < SMALL_SAMPLES ? 0 : 1);
+    if (team[k]) {
+      b->bucket[key[k]].team++;
+      b->n_team++;
+      key[k] = -1;
+    }
+  }
+  std::vector<size_t> order(items.size());
+  std::iota(order.begin(), order.end(), 0);
+  std::stable_sort(order.begin(), order.end(), [&](size_t x, size_t y) {
+    return key[x] != key[y] ? key[x] < key[y] : size[x] > size[y];
+  });
+  sorted.resize(items.size());
+  for (size_t k = 0; k < order.size(); ++k) sorted[k] = items[order[k]];
+  for (size_t k = b->n_team; k < order.size(); ++k) {
+    Bucket& bk = b->bucket[key[order[k]]];
+    if (bk.count == 0) bk.begin = (int)k;
+    bk.count++;
+  }
 }
 
 void drop_graph(qc_batch* b) {
@@ -329,45 +382,29 @@ qc_status qc_batch_create(qc_ctx* ctx, const qc_problem* problems, int32_t n_pro
         items.push_back(it);
       }
   }
-  // the teams' items, then the buckets', largest first in each
-  std::vector<char> team;
-  choose_team(b, items, team);
-  std::vector<int> key(items.size());
-  std::vector<long long> size(items.size());
-  for (size_t k = 0; k < items.size(); ++k) {
-    const BatchItem& it = items[k];
-    const long long smp = (it.r_hi - it.r_lo) * (long long)(it.c_hi - it.c_lo);
-    size[k] = smp * (b->probs[it.prob].term.kind == KIND_C2X2 ? 2 : 1);
-    key[k] = width_class(it.c_hi - it.c_lo) * N_SIZE + (smp < SMALL_SAMPLES ? 0 : 1);
-    if (team[k]) {
-      b->bucket[key[k]].team++;
-      b->n_team++;
-      key[k] = -1;
-    }
-  }
-  std::vector<size_t> order(items.size());
-  std::iota(order.begin(), order.end(), 0);
-  std::stable_sort(order.begin(), order.end(), [&](size_t x, size_t y) {
-    return key[x] != key[y] ? key[x] < key[y] : size[x] > size[y];
-  });
-  std::vector<BatchItem> sorted(items.size());
-  for (size_t k = 0; k < order.size(); ++k) sorted[k] = items[order[k]];
-  for (size_t k = b->n_team; k < order.size(); ++k) {
-    Bucket& bk = b->bucket[key[order[k]]];
-    if (bk.count == 0) bk.begin = (int)k;
-    bk.count++;
-  }
-  b->n_items = (int)sorted.size();
   int dev_cu = 0;
   HIP_TRY(ctx, hipDeviceGetAttribute(&dev_cu, hipDeviceAttributeMultiprocessorCount, ctx->device));
   b->n_cu = std::max(dev_cu, 1);
+  // the teams' items, then the buckets', largest first in each
+  std::vector<char> team;
+  choose_team(b, items, team);
+  std::vector<BatchItem> sorted;
+  arrange(b, items, team, sorted);
+  qc_status st = make_team(b, sorted);
+  if (st == QC_E_NOMEM) {                       // the buckets need none: every interval to them
+    team.assign(items.size(), 0);
+    arrange(b, items, team, sorted);
+    st = QC_OK;
+  }
+  if (st != QC_OK) return bail(st);
+  b->n_items = (int)sorted.size();
   // 4 rows per step in every bucket (as the single-term solve), 8 wavefronts per
   // workgroup where the intervals do not fill the chip several times over: on
   // batches of 10 to 96 problems the autotuner took these for all but one
   // bucket, and the graph went from 50.0 to 25.0 ms (24 problems) against 2 or 4
   // wavefronts and 4, 2 or 1 rows by width
   for (int i = 0; i < N_BUCKET; ++i) {
-    qc_status st = bucket_config(b, b->bucket[i], b->bucket[i].count >= 8 * b->n_cu ? 4 : 8, 4);
+    st = bucket_config(b, b->bucket[i], b->bucket[i].count >= 8 * b->n_cu ? 4 : 8, 4);
     if (st != QC_OK && b->bucket[i].count < 8 * b->n_cu) st = bucket_config(b, b->bucket[i], 4, 4);
     if (st != QC_OK) return bail(st);
   }
@@ -379,8 +416,6 @@ qc_status qc_batch_create(qc_ctx* ctx, const qc_problem* problems, int32_t n_pro
   HIP_TRY(ctx, hipMemcpy(b->d_probs, b->probs.data(), sizeof(BatchProb) * b->probs.size(), hipMemcpyHostToDevice));
   if (!sorted.empty())
     HIP_TRY(ctx, hipMemcpy(b->d_items, sorted.data(), sizeof(BatchItem) * sorted.size(), hipMemcpyHostToDevice));
-  qc_status st = make_team(b, sorted);
-  if (st != QC_OK) return bail(st);
   if (hipStreamCreateWithFlags(&b->cs, hipStreamNonBlocking) != hipSuccess)
     return bail(fail(ctx, QC_E_DEVICE, "stream"));
   for (int i = 0; i <= N_BUCKET; ++i)
@@ -567,10 +602,7 @@ qc_status qc_batch_destroy(qc_batch* b) {
   hipFree(b->d_probs);
   hipFree(b->d_items);
   hipFree(b->d_queue);
-  hipFree(b->d_team);
-  hipFree(b->d_team_words);
-  hipFree(b->d_team_parts);
-  hipFree(b->d_team_dv);
+  drop_team(b);
   for (int i = 0; i <= N_BUCKET; ++i) {
     if (b->bs[i]) hipStreamDestroy(b->bs[i]);
     if (b->join[i]) hipEventDestroy(b->join[i]);

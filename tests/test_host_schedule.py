@@ -33,3 +33,15 @@ def test_spare_buffers_grow_within_the_limits():
     for buf in ("d_fold", "d_ptab", "d_outtab"):
         assert re.search(r"spare_memory\(ctx, ctx->%s\b" % buf, text), buf
         assert not re.search(r"grow\(ctx->%s\b" % buf, text), buf
+
+
+def test_batch_teams_give_way_to_the_buckets():
+    """The teams' memory is asked for within the limits, and a batch without it goes
+    to the buckets instead of failing."""
+    text = open(os.path.join(CSRC, "qc_batch_api.hip")).read()
+    make = text[text.index("qc_status make_team("):]
+    make = make[:make.index("\n}\n")]
+    assert make.index("spare_fits(") < make.index("hipMalloc(")
+    create = text[text.index("qc_status qc_batch_create("):]
+    assert re.search(r"st = make_team\(b, sorted\);\s+if \(st == QC_E_NOMEM\) \{[^}]*arrange\(b, items, team, sorted\);"
+                     r"\s+st = QC_OK;", create)
