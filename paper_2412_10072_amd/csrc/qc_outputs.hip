@@ -258,7 +258,8 @@ __global__ void __launch_bounds__(256) k_outputs(OutputLaunch L) {
     // before the first is written (the chain and the store of one step would
     // hold back the read of the next; 64 antennas, 50 x 1024: 803 -> 675 us)
     if (L.w_vec) {
-      using W4 = S __attribute__((ext_vector_type(4)));
+      // (w_vec promises 16 bytes; four doubles would claim 32)
+      typedef S W4 __attribute__((ext_vector_type(4), aligned(16)));
       const W4* Wp = reinterpret_cast<const W4*>(V.weight);
       W4* Ow = reinterpret_cast<W4*>(L.out);
       constexpr int U = 4;

@@ -71,3 +71,27 @@ def test_weights_and_flags(qc_lib, n_chan, n_wcorr, dtype):
         f_odd, n_odd, _ = qc_lib.mad_flag(odd, shifted(r), mode=mode, k=6.0)
         want, _ = o_flag.mad_flag(vis, resid, 6.0, mode)
         assert np.array_equal(f.cpu().numpy(), want) and torch.equal(f, f_odd) and n_new == n_odd
+
+
+@pytest.mark.parametrize("n_chan", [63, 130, 257])
+def test_corrected_weights_at_odd_multiples_of_16_bytes(qc_lib, n_chan):
+    """Four double weights per sample that begin 16 bytes past a 32-byte boundary (what
+    the four-weight path promises to take): bitwise the aligned arrays' results."""
+    from paper_2412_10072_amd import qc
+    say(f"corrected weights 16 mod 32, {n_chan} channels")
+    rng = np.random.default_rng(n_chan)
+    vis = make_vis(rng, n_ant=5, n_time=4, n_chan=n_chan)
+    term = make_term(rng, "diag", 4, n_chan, 5, t_int=2, f_int=40, scale=0.2)
+    v, t = qc.device_vis(vis, DEV), qc.device_term(term, DEV)
+
+    def by_16(x):
+        flat = torch.empty(x.numel() + 2, dtype=x.dtype, device=x.device)[2:]
+        assert flat.data_ptr() % 32 == 16
+        flat.copy_(x.reshape(-1))
+        return flat.view(x.shape)
+    want = qc_lib.corrected_weights(v, [t])
+    for w, out in ((by_16(v.weight), torch.empty_like(want)), (v.weight, by_16(want)), (by_16(v.weight), by_16(want))):
+        out.zero_()
+        assert torch.equal(qc_lib.corrected_weights(v.copy(weight=w), [t], out=out), want)
+    ref = o_rob.corrected_weights(vis, [term])
+    assert (np.abs(want.cpu().numpy() - ref) <= 1e-12 * np.abs(ref)).all()
