@@ -34,7 +34,17 @@
  * - Work is enqueued on `stream` (NULL = the null stream).  The argument
  *   checks that need device data (row_time order, antenna and map ranges)
  *   run first on the same stream and are waited for, so a call that returns
- *   QC_OK has passed them.  The solve itself is asynchronous.
+ *   QC_OK has passed them.  The work itself is asynchronous, except that a
+ *   solve on the split schedule (qc_ctx_set_split; chosen for many sizes) holds
+ *   the host until all but its last pass have run: results are read after
+ *   the stream, not after the call, in either case.
+ * - A context may be used on several streams by its one host thread.  Its solves
+ *   share scratch memory and so do its outputs (qc_apply_gains, qc_residual,
+ *   qc_corrected_weights) whose chain is tabulated: such a call waits on the
+ *   device for the last one on another stream.  The scratch of qc_delay_init,
+ *   qc_ws_features, qc_mlp_backward, qc_mad_flag, qc_robust_weights and of
+ *   predicted models is not guarded: calls of one of these on different
+ *   streams of one context are ordered by the caller.
  */
 #ifndef QC_H
 #define QC_H
@@ -64,8 +74,9 @@ typedef enum { QC_PREC_FP64 = 0, QC_PREC_MIXED = 1 } qc_prec;
 /* QC_PREC_FP64 : every product, sum and solve in FP64 (complex64 inputs are
  *                upcast exactly).
  * QC_PREC_MIXED: complex64 products and residuals, FP32 accumulation with
- *                compensated (Kahan) sums of the per-antenna blocks, FP64
- *                block solve, update and convergence test.  Needs QC_C64.   */
+ *                compensated (Kahan) sums of the per-antenna blocks (FP64 sums
+ *                over intervals of one channel each), FP64 block solve, update
+ *                and convergence test.  Needs QC_C64.                       */
 
 typedef enum {
   QC_TERM_DIAGONAL = 0, QC_TERM_COMPLEX2X2 = 1, QC_TERM_DELAY = 2, QC_TERM_PHASE = 3, QC_TERM_AMPLITUDE = 4,
@@ -155,18 +166,21 @@ double      qc_last_kernel_ms(qc_ctx* ctx);
  * and size of the intervals, 4 in the split schedule) and rows per
  * wavefront step (1, 2, 4; 0 = 4 rows of 16 lanes).
  * Multi-row steps apply to single-term, single-direction chains only.
- * rows_per_step 8 sets the split schedule of one-channel intervals (a
- * bandpass per channel on a diagonal chain) to steps of 8 rows x 8 channels
- * instead of 4 rows x 16 channels, and leaves the other kernels at their
- * default. */
+ * The split schedule of one-channel intervals (a bandpass per channel on a
+ * diagonal chain) takes steps of 4 rows x 16 channels or 8 x 8, by the antennas;
+ * rows_per_step 4 and 8 set one or the other (4 x 16 while its sums fit), and 8
+ * leaves the other kernels at their default. */
 qc_status   qc_ctx_set_tile(qc_ctx* ctx, int32_t waves, int32_t rows_per_step);
-/* Schedule of qc_solve_interval: parts = 0 chooses automatically (a term with
- * fewer intervals than four times the compute units, of >= 2^18 samples on
- * average, is split into about 32 workgroups per compute unit; not with a
- * chisq_ref), 1 never splits (one workgroup runs each interval to the end),
- * > 1 cuts every interval's rows into that many parts streamed by separate
- * workgroups whose FP64 blocks are summed in a fixed order before each update
- * (the host then waits on the device once per iteration). */
+/* Schedule of qc_solve_interval: parts = 0 chooses automatically, by an estimate
+ * of one pass of either schedule from the number and size of the intervals (terms
+ * with fewer intervals than four times the compute units, of >= 2^18 samples on
+ * average, are always split; Levenberg-Marquardt splits those only, a solve with a
+ * chisq_ref never; nor is one split without free memory for the partial sums, 2 GiB
+ * at most).  1 never splits (one workgroup runs each interval to the end).  > 1
+ * cuts every interval's rows into that many parts streamed by separate
+ * workgroups whose FP64 blocks are summed in a fixed order before each update; the
+ * host launches one pass ahead of the one it waits for, and the automatic choice
+ * takes 4 to 32 workgroups per compute unit. */
 qc_status   qc_ctx_set_split(qc_ctx* ctx, int32_t parts);
 /* Parts per interval of the last qc_solve_interval (1 = not split). */
 int32_t     qc_ctx_last_split(const qc_ctx* ctx);
@@ -257,11 +271,15 @@ typedef struct {
  * for COMPLEX2X2, 2x2 for DIAGONAL, real 2x2 for DELAY / PHASE / AMPLITUDE,
  * real 4x4 for DELAY_OFFSET, whose pivots are then each tested against their
  * own diagonal entry), one row per wavefront step.
- * The context keeps scratch memory between calls.  Its largest part is the
- * folded model of a diagonal chain (one direction of the model's size, where
- * the active term has one gain direction): at most a sixteenth of the device's
- * memory and an eighth of what was free when it was allocated; without room the
- * solve reads the model itself.  qc_ctx_destroy gives it back.
+ * The context keeps scratch memory between calls and qc_ctx_destroy gives it back.
+ * What it can do without it takes within limits: the folded model of a diagonal
+ * chain (one direction of the model's size, where the active term has one gain
+ * direction), the phasors of an FP64 delay term and the outputs' chain table (1
+ * GiB at most) up to a sixteenth of the device's memory and an eighth of what was
+ * free when they were allocated, else the solve reads the model itself and the
+ * rest is formed per sample; the partial sums of an automatic split up to half of
+ * what was free.  The tables of a chain's fixed terms and the state of the split
+ * schedule have no limit beyond the device's.
  */
 qc_status qc_solve_interval(qc_ctx* ctx, const qc_vis* vis, qc_term* chain, int32_t n_term,
                             int32_t active, const qc_solve_opts* opts, qc_solve_stats* stats);

@@ -427,7 +427,6 @@ __global__ void __launch_bounds__(256) k_band_gains(const double2* gains, int n_
   tab[i] = cmake<T>((T)g.x, (T)g.y);
 }
 
-template <typename T>
 struct BandRow {
   int p, q, t;               // of this lane's row; q = -1: the row adds nothing
 };
@@ -523,21 +522,21 @@ __global__ void __launch_bounds__(64) k_band_single(SolveLaunch L, int n_part, d
 
   // row of this lane in the step that begins at row r (clamped into the part)
   auto row_at = [&](long long r) -> long long { return min(r + g, r_hi - 1); };
-  auto load_row = [&](long long r) -> BandRow<T> {
+  auto load_row = [&](long long r) -> BandRow {
     const long long rr = row_at(r);
-    BandRow<T> a{V.ant1[rr], V.ant2[rr], V.row_time[rr]};
+    BandRow a{V.ant1[rr], V.ant2[rr], V.row_time[rr]};
     const bool ok = r + g < r_hi && a.p != a.q && (unsigned)a.p < (unsigned)n_ant && (unsigned)a.q < (unsigned)n_ant;
     a.p = ok ? a.p : 0;
     a.q = ok ? a.q : -1;
     return a;
   };
-  auto load_gain = [&](const BandRow<T>& a) -> BandGain<T> {
+  auto load_gain = [&](const BandRow& a) -> BandGain<T> {
     const cx<T>* hp = tab + (size_t)a.p * 2 * CW + cl;
     const cx<T>* hq = tab + (size_t)max(a.q, 0) * 2 * CW + cl;
     return {hp[0], hp[CW], hq[0], hq[CW]};
   };
   RawSample<S> x0 = {}, x1 = {}, x2 = {};
-  BandRow<T> a0{0, -1, 0}, a1{0, -1, 0}, a2{0, -1, 0};
+  BandRow a0{0, -1, 0}, a1{0, -1, 0}, a2{0, -1, 0};
   BandGain<T> h0 = {}, h1 = {};
   auto load_x = [&](RawSample<S>& x, long long r) {
     raw_load<S>(x, Dp, Mp, Wp, V.flag, (size_t)row_at(r) * n_chan + cc, V.n_wcorr);
