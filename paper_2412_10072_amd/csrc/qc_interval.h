@@ -2326,7 +2326,8 @@ __device__ __forceinline__ void split_update_lm(const Job& J, const double* tot,
     }
     if (J.gflags) {
       int f = attempt ? gfl[slot] : (int)J.gflags[dst];
-      if (f == 0 && finish && !conv && dv[2 * slot] >= (double)DIV_RUN) f = 2;   // updates did not tend to zero
+      // updates did not tend to zero (att 0: there was none, and dv is not set)
+      if (f == 0 && finish && !conv && att > 0 && dv[2 * slot] >= (double)DIV_RUN) f = 2;
       J.gflags[dst] = (int8_t)f;
     }
   });
