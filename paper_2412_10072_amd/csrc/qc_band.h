@@ -8,8 +8,8 @@
 // at the row stride.  Here a wavefront takes 16 neighbouring channels -- 16
 // intervals -- and steps through a part of their rows four rows at a time,
 // lane (g, c) = (row g of the step, channel c) (or 8 channels and 8 rows,
-// whose LDS slots are half as large: for arrays whose 16-channel slots do not
-// fit).  Every sample load is then a contiguous segment of channels, and the
+// whose LDS slots are half as large: where 16-channel slots do not fit or leave
+// too few wavefronts).  Every sample load is then a contiguous segment of channels, and the
 // intervals need no reduction across lanes: each lane's channel is its own
 // interval.
 //
@@ -63,9 +63,9 @@ __device__ __forceinline__ A* band_slot(int ant, int k, int cl) {
 // Adds a lane's values to the slots of (ant, channel cl).  The lanes of one call
 // address distinct slots and only this wavefront does, so plain reads and writes
 // do: as LDS atomics (six per step, rows colliding on banks) the additions were
-// what bounded the pass, at 2.2 TB/s whatever was loaded ahead (1.24 ms for 256
-// channels x 60 times of 64 antennas, with these 0.68, and 0.55 in one round of
-// workgroups).
+// what bounded the pass, at 2.2 TB/s whatever was loaded ahead (FP32 slots, 256
+// channels x 60 times of 64 antennas: 1.24 ms, with these 0.68, and 0.55 in one round
+// of workgroups).
 template <typename A, int CW>
 __device__ __forceinline__ void band_add(int ant, int cl, const A* v) {
   using A2 = A __attribute__((ext_vector_type(2)));
@@ -398,8 +398,8 @@ __global__ void __launch_bounds__(64) k_band_pass(SolveLaunch L, int n_part, dou
 // The same pass where the model is one direction and the chain the active term
 // alone (as it is over a folded chain): no fixed factors.
 //
-// Bound by latency: six wavefronts per CU (24 KiB of LDS each at 64 antennas)
-// and 64 samples a step.  So a step is simply the next four (eight) rows, whose
+// Bound by latency: six wavefronts per CU (24 KiB of LDS each at 64 antennas, in
+// steps of 8 x 8) and 64 samples a step.  So a step is simply the next four (eight) rows, whose
 // samples are loaded two steps ahead and whose antennas and gains one step ahead
 // (the steps above wait for one another's records), and the gains come from a
 // table in the step's own layout [gain time][slice][antenna][hand][channel]
@@ -407,7 +407,8 @@ __global__ void __launch_bounds__(64) k_band_pass(SolveLaunch L, int n_part, dou
 // of the solution's FP64 blocks, which lie an interval apart).  The rows of a step
 // may differ in antenna p: each lane keeps its own row's p sums and adds them to
 // LDS, one row after the other, when its p changes.  Folded bandpass of 256
-// channels, 64 antennas, 60 times (2.5 GB a pass): 1.24 -> 0.55 ms.
+// channels, 64 antennas, 60 times (2.5 GB a pass): 1.24 -> 0.55 ms with FP32 slots; the
+// mean over a solve's passes 0.46 ms with those, 0.52 with the FP64 ones (4.8 TB/s).
 // ---------------------------------------------------------------------------
 template <typename T, int CW>
 __global__ void __launch_bounds__(256) k_band_gains(const double2* gains, int n_gf, int n_ant, int n_slices, size_t n,

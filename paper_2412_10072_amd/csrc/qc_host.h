@@ -28,9 +28,10 @@ constexpr double SPLIT_PART_SAMPLES = 32768.0;
 constexpr double SPLIT_MIN_SAMPLES = 512.0;
 constexpr double SPLIT_MIN_ROWS = 16.0;
 // Wavefronts per compute unit that the split over one-channel intervals aims
-// at: one round of as many as the LDS holds (24 KiB each at 64 antennas and FP32:
-// six), at most two per SIMD for the registers.  512 channels x 100 times: 6 per
-// CU 51.8 ms a solve, 4 61.7, 8 71.8, 12 54.2, 24 64.1.
+// at: one round of as many as the LDS holds (24 KiB each at 64 antennas in steps of
+// 8 x 8: six), at most two per SIMD for the registers.  64 antennas, 100 times x
+// 512 channels, 10 updates: 6 per CU 19.0 ms, 3 30.1, 4 24.7, 5 20.3, 7 29.1, 8
+// 25.8, 12 20.1, 24 20.5.
 constexpr int BAND_WAVES_PER_CU = 8;
 
 // Context scratch that a call's kernels may still read after the call returned.  A

@@ -28,11 +28,6 @@
 namespace qc {
 namespace {
 
-// The row form where its lanes are at most this many times the channels: 16
-// channels (40 antennas, 100 times) take 67 us by rows and 31 flat, 83 channels
-// (1.54 times as many lanes) 418 and 399.
-constexpr double FLAT_LANES = 1.3;
-
 template <typename S, typename T>
 __device__ __forceinline__ m22<T> ld(const S* base, size_t elem) {
   if constexpr (sizeof(S) == 4) {
@@ -350,7 +345,7 @@ __global__ void __launch_bounds__(256) k_out_table(OutputLaunch L, cx<T>* out) {
 template <typename S, int MODE, bool DIAG, bool SKY>
 hipError_t launch_mode(const OutputLaunch& L, hipStream_t stream) {
   const long long n_row = L.vis.n_row, n_chan = L.vis.n_chan;
-  const bool flat = (double)((n_chan + 63) / 64 * 64) > FLAT_LANES * (double)n_chan;
+  const bool flat = flat_samples(n_chan);
   const long long steps = flat ? (n_row * n_chan + 63) / 64 : n_row;     // of a wavefront
   const dim3 g((unsigned)std::min<long long>((steps + 3) / 4, 256 * 64)), b(256);
   if constexpr (!SKY) {

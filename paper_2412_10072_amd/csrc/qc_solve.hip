@@ -252,7 +252,7 @@ template <typename T>
 hipError_t launch_fold(const SolveLaunch& L, void* out, hipStream_t stream) {
   const long long n_row = L.vis.n_row, n_chan = L.vis.n_chan;
   if (n_row == 0 || n_chan == 0) return hipSuccess;
-  const bool flat = (n_chan + 63) / 64 * 64 * 10 > 13 * n_chan;          // as the outputs (FLAT_LANES)
+  const bool flat = flat_samples(n_chan);
   const long long steps = flat ? (n_row * n_chan + 63) / 64 : n_row;
   const dim3 g((unsigned)std::min<long long>((steps + 3) / 4, 256 * 64)), b(256);
   if (flat) hipLaunchKernelGGL((k_chain_fold<T, true>), g, b, 0, stream, L, reinterpret_cast<T*>(out));
