@@ -39,6 +39,7 @@ constexpr int BAND_WAVES_PER_CU = 8;
 struct ScratchUse {
   hipEvent_t ev = nullptr;             // after the last reader: the call's end event (call_end)
   hipStream_t stream = nullptr;
+  bool used = false;
 };
 
 struct qc_ctx {
@@ -176,7 +177,7 @@ hipError_t grow(P*& ptr, size_t& cap, size_t n) {
 
 // Before `s` writes that scratch.
 inline hipError_t scratch_take(const ScratchUse& u, hipStream_t s) {
-  return u.stream != s ? hipStreamWaitEvent(s, u.ev, 0) : hipSuccess;
+  return u.used && u.stream != s ? hipStreamWaitEvent(s, u.ev, 0) : hipSuccess;
 }
 // Before a call on `s` clears the error word; writes_ranges: and rewrites the interval
 // ranges and what else a solve uses.
@@ -188,8 +189,11 @@ inline hipError_t solve_take(const qc_ctx* ctx, hipStream_t s, bool writes_range
 // solve 30 of 390 us).
 inline hipError_t call_end(qc_ctx* ctx, hipStream_t s, ScratchUse* use = nullptr) {
   ctx->ev_end = use ? use->ev : ctx->ev1;
-  if (use) use->stream = s;
   const hipError_t e = hipEventRecord(ctx->ev_end, s);
+  if (use) {
+    use->stream = s;
+    use->used = e == hipSuccess;
+  }
   ctx->timed = e == hipSuccess;
   return e;
 }

@@ -67,6 +67,29 @@ def test_outputs_with_tables_on_two_streams(qc_lib):
         torch.cuda.synchronize()
 
 
+def test_first_calls_of_a_context_on_a_side_stream():
+    """Nothing of the context is in use yet: a solve and a tabulated residual on a
+    stream of their own give what they give on the default stream."""
+    from paper_2412_10072_amd import qc
+    say("first calls on a side stream")
+    vis, term = device_problem(31, 24, 20, 64, 1, 1)
+    start = term.gains.clone()
+    out = []
+    for stream in (None, torch.cuda.Stream()):
+        ctx = qc.Context(0)
+        term.gains.copy_(start)
+        torch.cuda.synchronize()
+        r = torch.empty_like(vis.data)
+        torch.cuda.synchronize()
+        ctx.residual(vis, [term], out=r, stream=stream)
+        ctx.solve(vis, [term], 0, tol=-1.0, max_iter=2, prec="mixed", stream=stream)
+        assert ctx.last_kernel_ms() > 0.0
+        torch.cuda.synchronize()
+        out.append((r, term.gains.clone()))
+        ctx.close()
+    assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
+
+
 def test_split_solves_on_two_streams(qc_lib):
     """Solves that stop at max_iter with their last pass in flight, beside one
     another and beside a residual: unlike sizes, so that every range, block count and
