@@ -133,3 +133,26 @@ def test_team_intervals(qc_lib, dtype, prec):
         assert e <= (1e-10 if prec == "fp64" else 1e-4)
         assert (st["iters"].cpu().numpy() == 3).all()
     b.close()
+
+
+@pytest.mark.parametrize("k", [2, 3])
+@pytest.mark.parametrize("n_ant", [35, 36, 86, 171, 256])
+def test_band_pass_by_antennas(ctx, n_ant, k):
+    """The antenna counts where the step's shape and the LDS limit change (MIXED 4 x 16
+    steps to 35, 8 x 8 beyond, over 64 KiB from 171; FP64 to 170), the band pass over
+    the chain (2 updates) and over the folded model (3)."""
+    from paper_2412_10072_amd import qc
+    say(f"band pass, {n_ant} antennas, {k} updates")
+    rng = np.random.default_rng(n_ant)
+    n_chan, n_dir = 3, 2
+    vis = make_vis(rng, n_ant=n_ant, n_time=1, n_chan=n_chan, n_dir=n_dir, polarised=False)
+    vis.data = vis.model.sum(axis=2) + 0.1 * rand_c(rng, *vis.data.shape)
+    vis = vis.copy(data=vis.data.astype(np.complex64), model=vis.model.astype(np.complex64),
+                   weight=vis.weight.astype(np.float32))
+    chain = [make_term(rng, "phase", 1, n_chan, n_ant, n_dir=n_dir, scale=0.02),
+             unit_like(make_term(rng, "diag", 1, n_chan, n_ant, f_int=1, n_dir=n_dir))]
+    solve_and_check(ctx, vis, chain, "mixed", k, 3)
+    assert ctx.last_route() == qc.ROUTE_SPLIT | qc.ROUTE_BAND | (qc.ROUTE_FOLD if k >= 3 else 0)
+    if k == 2:
+        solve_and_check(ctx, vis, chain, "fp64", k, 3)
+        assert ctx.last_route() == qc.ROUTE_SPLIT | (qc.ROUTE_BAND if n_ant <= 170 else 0)
